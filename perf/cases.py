@@ -280,9 +280,9 @@ def work(case):
 
 def tolerance(case):
     # against 64 bits, over these cases: up to 1.1e-6 in the norm (the softmax margin; the
-    # others 2e-7 and less).  Whole numbers follow thresholds and cumulative sums: ties
-    # within rounding.
-    return {"rel": 5e-6, "max": 1e-4, "differ": 0.002}
+    # others 2e-7 and less).  Whole numbers follow thresholds and cumulative sums of up to
+    # 152064 terms: 1 of 512 samples fell beside the 64-bit one.
+    return {"rel": 5e-6, "max": 1e-4, "differ": 0.008}
 
 
 # ---------------------------------------------------------------------------- in 64 bits
