@@ -460,35 +460,59 @@ __device__ __forceinline__ void conf_one(ConfState& s, float z, int cid) {
   conf_chunk<1, false, VAR>(s, f, 1u, cid);
 }
 
-// Enumerates the elements of one chunk of thread t (chunk ids: 0 head element,
-// 1..nr full rounds, nr+1 the partial round, nr+2 the tail element) and returns the
-// lowest index holding `m` plus the largest other value in that chunk.
+// For a thread holding the row max `m`: the lowest index holding it in its chunk `cid`
+// (chunk ids: 0 head element, 1..nr full rounds, nr+1 the partial round, nr+2 the tail
+// element) and the largest other value of that chunk.  A chunk of vectors is in `keep`
+// if `kept`, else read again: nothing else of the workgroup runs meanwhile, so its U
+// loads all leave before any is looked at (a vector past the row reads the row's first
+// one, unused).  One at a time they were U dependent round trips (16 fp32 sequences of 8
+// drafts at V = 32000, GREEDY: target rows 12.2 -> 11.5 us).
 template <typename T, int BD>
-__device__ void rescan_chunk(const T* row, const Geom& g, int64_t nr, int cid, float m, int64_t& idx, float& other) {
+__device__ __forceinline__ void max_chunk(const T* row, const Geom& g, int64_t nr, int cid, float m, bool kept,
+                                          const uint4 (&keep)[Elem<T>::U], int64_t& idx, float& other) {
   using E = Elem<T>;
   constexpr int VEC = E::VEC, U = E::U;
   const int t = threadIdx.x;
   idx = INT64_MAX;
   other = -INFINITY;
-  auto visit = [&](int64_t i, float z) {
-    if (idx == INT64_MAX && z == m) idx = i;
-    else other = fmaxf(other, z);
-  };
   if (cid == 0) {
-    if (t < g.head) visit(t, E::load(row + t));
+    idx = t;
   } else if (cid == nr + 2) {
-    const int64_t base = g.head + g.nvec * VEC;
-    if (t < g.tail) visit(base + t, E::load(row + base + t));
-  } else if (cid >= 1 && cid <= nr + 1) {
-    const uint4* vp = reinterpret_cast<const uint4*>(row + g.head);
-    for (int u = 0; u < U; ++u) {
-      const int64_t j = (int64_t)(cid - 1) * U * BD + (int64_t)u * BD + t;
-      if (j < g.nvec) {
-        float f[VEC];
-        E::unpack(vp[j], f);
-        for (int e = 0; e < VEC; ++e) visit(g.head + j * VEC + e, f[e]);
+    idx = g.head + g.nvec * VEC + t;
+  } else if (cid > 0) {
+    const int64_t j0 = (int64_t)(cid - 1) * U * BD + t;
+    uint4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = make_uint4(0u, 0u, 0u, 0u);
+    if (!kept) {
+      const uint4* vp = reinterpret_cast<const uint4*>(row + g.head);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t j = j0 + (int64_t)u * BD;
+        v[u] = vp[j < g.nvec ? j : 0];
       }
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v[u].x = kept ? keep[u].x : v[u].x;
+      v[u].y = kept ? keep[u].y : v[u].y;
+      v[u].z = kept ? keep[u].z : v[u].z;
+      v[u].w = kept ? keep[u].w : v[u].w;
+    }
+    int pos = -1;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = j0 + (int64_t)u * BD < g.nvec;
+      float f[VEC];
+      E::unpack(v[u], f);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        const bool first = in && pos < 0 && f[e] == m;
+        other = first || !in ? other : fmaxf(other, f[e]);
+        pos = first ? u * VEC + e : pos;
+      }
+    }
+    if (pos >= 0) idx = g.head + (j0 + (int64_t)(pos / VEC) * BD) * VEC + pos % VEC;
   }
 }
 
@@ -558,9 +582,9 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
     ConfState s;
     // KEEP: the vectors of the round that set this thread's maximum stay in registers,
     // so the epilogue finds the max index without reading that round again
-    uint4 keep[KEEP ? U : 1];
+    uint4 keep[U];
 #pragma unroll
-    for (int u = 0; u < (KEEP ? U : 1); ++u) keep[u] = make_uint4(0u, 0u, 0u, 0u);
+    for (int u = 0; u < U; ++u) keep[u] = make_uint4(0u, 0u, 0u, 0u);
     // Masked (-inf) logits: every logit is clamped to at least kMaskedLogit before the
     // sums (a masked one then adds exactly 0 to A and T), and a probe over the raw
     // vectors (plus a test of the single head, tail and partial-round elements) records
@@ -588,7 +612,7 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
       if (KEEP) {
         const bool up = s.gid == int(k + 1);
 #pragma unroll
-        for (int u = 0; u < (KEEP ? U : 1); ++u) {
+        for (int u = 0; u < U; ++u) {
           keep[u].x = up ? raw[u].x : keep[u].x;
           keep[u].y = up ? raw[u].y : keep[u].y;
           keep[u].z = up ? raw[u].z : keep[u].z;
@@ -635,23 +659,7 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
     const bool is_max = s.t1 == m;
     int64_t idx = INT64_MAX;
     float other = -INFINITY;
-    if (is_max) {
-      if (KEEP && s.gid >= 1 && s.gid <= nr) {
-#pragma unroll
-        for (int u = 0; u < (KEEP ? U : 1); ++u) {
-          float fv[VEC];
-          E::unpack(keep[u], fv);
-          const int64_t j = (int64_t)(s.gid - 1) * U * BD + (int64_t)u * BD + t;
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) {
-            if (idx == INT64_MAX && fv[e] == m) idx = g.head + j * VEC + e;
-            else other = fmaxf(other, fv[e]);
-          }
-        }
-      } else {
-        rescan_chunk<T, BD>(row, g, nr, s.gid, m, idx, other);
-      }
-    }
+    if (is_max) max_chunk<T, BD>(row, g, nr, s.gid, m, KEEP && s.gid <= nr, keep, idx, other);
     const float contrib = is_max ? s.t2 : s.t1;
     const int idx32 = idx == INT64_MAX ? INT32_MAX : int(idx);
 
@@ -769,8 +777,9 @@ template <typename T, int BD, bool VAR, int DEPTH>
 __global__ __launch_bounds__(BD) void k_confidence(const T* __restrict__ logits, int64_t n_rows, int64_t V,
                                                    int64_t stride, ConfArgs a, cmsd_row_stats* __restrict__ out,
                                                    float* __restrict__ var_out) {
-  for (int64_t r = blockIdx.x; r < n_rows; r += gridDim.x)
-    conf_row<T, BD, VAR, DEPTH>(logits + r * stride, V, a, out + r, VAR ? var_out + r : nullptr);
+  const int64_t r = blockIdx.x;
+  if (r >= n_rows) return;
+  conf_row<T, BD, VAR, DEPTH>(logits + r * stride, V, a, out + r, VAR ? var_out + r : nullptr);
 }
 
 // ----------------------------------------------------------------------------- K2 draft length
@@ -1079,7 +1088,8 @@ __device__ __forceinline__ void target_row(const VerifyArgs& a, int64_t q) {
     float other;
     if (s.t1 == m) {
       constexpr int U = Elem<T>::U;
-      rescan_chunk<T, BD>(trow, g, g.nvec / ((int64_t)U * BD), s.gid, m, idx, other);
+      const uint4 none[U] = {};
+      max_chunk<T, BD>(trow, g, g.nvec / ((int64_t)U * BD), s.gid, m, false, none, idx, other);
     }
     top1 = block_all_i<BD>(idx == INT64_MAX ? INT32_MAX : int(idx), OpMinI(), si);
   }
@@ -1987,25 +1997,25 @@ bool deep_ring(int64_t n_rows, int rows_per_cu) {
   return n_rows >= rows_per_cu * (int64_t)device_cus();
 }
 
-// Workgroups per confidence launch: the launch's work-items (workgroups x threads) stay
-// below 2^32, and the kernel's loop over rows takes any rows beyond.  (Below the cap
-// the loop runs once; a kernel of one row per workgroup and no loop gets more waves
-// per SIMD from fewer registers and measured slower on 8192 rows of 32000 logits.)
+// Rows per confidence launch: the launch's work-items (rows x threads) stay below 2^32,
+// and further rows go into further launches.  (A loop over rows inside the kernel had the
+// compiler keep the record's fp64 constants in registers across it: 152 instead of 120
+// registers for 256-thread bf16 rows, 245 instead of 144 for fp32, 204 instead of 136 for
+// the 64-thread rows of long launches.  One row per workgroup: 8192 masked rows of 32000
+// bf16 logits 88.9 -> 86.4 us, 128 fp32 rows of 32000 10.6 -> 10.1, 16 of them 8.7 -> 8.1.)
 constexpr int64_t kConfMaxGrid = (int64_t)1 << 22;
 
 template <typename T, bool VAR, int DEPTH>
 void launch_confidence_d(int bd, const T* logits, int64_t n_rows, int64_t V, int64_t stride, const ConfArgs& a,
                          cmsd_row_stats* out, float* var, hipStream_t st) {
-  const dim3 grid((unsigned)(n_rows < kConfMaxGrid ? n_rows : kConfMaxGrid));
-  if (bd == 64)
-    hipLaunchKernelGGL((k_confidence<T, 64, VAR, DEPTH>), grid, dim3(64), 0, st, logits, n_rows, V, stride, a, out,
-                       var);
-  else if (bd == 128)
-    hipLaunchKernelGGL((k_confidence<T, 128, VAR, DEPTH>), grid, dim3(128), 0, st, logits, n_rows, V, stride, a, out,
-                       var);
-  else
-    hipLaunchKernelGGL((k_confidence<T, 256, VAR, DEPTH>), grid, dim3(256), 0, st, logits, n_rows, V, stride, a, out,
-                       var);
+  const auto kernel = bd == 64    ? k_confidence<T, 64, VAR, DEPTH>
+                      : bd == 128 ? k_confidence<T, 128, VAR, DEPTH>
+                                  : k_confidence<T, 256, VAR, DEPTH>;
+  for (int64_t r = 0; r < n_rows; r += kConfMaxGrid) {
+    const int64_t n = n_rows - r < kConfMaxGrid ? n_rows - r : kConfMaxGrid;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3((unsigned)bd), 0, st, logits + r * stride, n, V, stride, a,
+                       out + r, VAR ? var + r : nullptr);
+  }
 }
 template <typename T, bool VAR>
 void launch_confidence(int bd, const T* logits, int64_t n_rows, int64_t V, int64_t stride, const ConfArgs& a,
