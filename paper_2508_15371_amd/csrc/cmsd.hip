@@ -194,6 +194,14 @@ __device__ __forceinline__ uint4 ld_stream(const uint4* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// A raw buffer of 32-bit words (data format 4 in bits 18:15), and the nontemporal hint.
+constexpr int kBufferFlags = 0x00020000;
+constexpr int kBufferNt = 2;
+
+__device__ __forceinline__ uint4 select4(bool c, const uint4& a, const uint4& b) {
+  return make_uint4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
+}
+
 // ----------------------------------------------------------------------------- wave / block reductions
 // Wave64 all-reduce: DPP quad permutes and row mirrors inside each 16-lane row,
 // then the four row results are combined through readlane (uniform result).
@@ -307,61 +315,58 @@ __device__ __forceinline__ void block_sum_n(double (&v)[N], double* lds) {
   }
 }
 
-// Streams the nr full rounds of a row: round k is U vectors per thread at
-// vp[(k*U + u)*BD + t].  DEPTH rounds of loads are kept in flight in a ring of
-// registers (fully unrolled, so each slot is consumed and then refilled in place:
-// no register copies).  The main loop covers the rounds whose refills all exist, so
-// no load there sits behind a branch: the number of loads in flight is the same on
-// every path, and the wait before a round covers that round only while the later
-// rounds stay in flight.  The last rounds (fewer than 2*DEPTH) follow with guarded
-// refills; the first DEPTH are always requested.  prep() runs once the first loads
-// are issued (work that must precede the first round overlaps their latency);
-// consume(raw[U], k) is called in round order.
+// Streams the vectors of a row in rounds: round k is U vectors per thread at
+// vp[(k*U + u)*BD + t], the last one possibly partial.  DEPTH rounds of loads are kept in
+// flight in a ring of registers, each slot consumed and then refilled in place.  No load
+// sits behind a branch, so the number of loads in flight is the same on every path and
+// the wait before a round covers that round only while the later ones stay in flight.
+// The loads go through a buffer descriptor of the round, whose range check ends at the
+// row: lanes past it read zeros and no memory, so the partial round is in flight with the
+// others (not a round trip of its own at the end), a refill past the last round is free,
+// and the addresses cost no vector instruction.  prep() runs once the first loads are
+// issued (work that must precede the first round overlaps their latency);
+// consume(raw[U], k, last) is called in round order, `last` (std::true_type) for the
+// rounds that may be partial.  Against pointer loads with a guarded partial round behind
+// the ring: 136 bf16 rows of 32000 8.9 -> 7.8 us, 128 fp32 ones 10.2 -> 8.5, 3334 packed
+// target rows 41.4 -> 37.7, 8448 fp32 rows of 128256 616.5 -> 614.
 #ifndef CMSD_STREAM_DEPTH
 #define CMSD_STREAM_DEPTH 2
 #endif
 template <int U, int BD, int DEPTH, typename P, typename F>
-__device__ __forceinline__ void stream_rounds(const uint4* vp, int64_t nr, int t, P&& prep, F&& consume) {
-  if (nr <= 0) {
+__device__ __forceinline__ void stream_rounds(const uint4* vp, int64_t nvec, int t, P&& prep, F&& consume) {
+  constexpr int64_t kRound = (int64_t)U * BD;
+  const int64_t nt = (nvec + kRound - 1) / kRound;
+  if (nt <= 0) {
     prep();
     return;
   }
-  // the first DEPTH rounds, issued unconditionally (a row of fewer rounds reads vp[0],
-  // the same 16 bytes for every lane, in their place)
   uint4 buf[DEPTH][U];
+  auto refill = [&](int d, int64_t k) {
+    const int64_t left = nvec - k * kRound;  // vectors of the row from this round on
+    const int bytes = 16 * int(left < 0 ? 0 : (left < kRound ? left : kRound));
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(vp) + k * kRound, 0, bytes, kBufferFlags);
 #pragma unroll
-  for (int d = 0; d < DEPTH; ++d) {
+    for (int u = 0; u < U; ++u) {
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, t * 16, u * BD * 16, kBufferNt);
+      buf[d][u] = make_uint4(v.x, v.y, v.z, v.w);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // rounds leave in order, before the next one is consumed
+  };
 #pragma unroll
-    for (int u = 0; u < U; ++u) buf[d][u] = ld_stream(vp + (d < nr ? ((int64_t)d * U + u) * BD + t : 0));
-    __builtin_amdgcn_sched_barrier(0);  // rounds leave in order, as the loop refills them
-  }
+  for (int d = 0; d < DEPTH; ++d) refill(d, d);
   prep();
   int64_t k0 = 0;
-  for (; k0 + 2 * DEPTH <= nr; k0 += DEPTH) {
+  for (; k0 + DEPTH < nt; k0 += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
-      const int64_t k = k0 + d;
-      consume(buf[d], k);
-      const int64_t kn = k + DEPTH;
-#pragma unroll
-      for (int u = 0; u < U; ++u) buf[d][u] = ld_stream(vp + (kn * U + u) * BD + t);
-      __builtin_amdgcn_sched_barrier(0);  // the refill leaves before the next round is consumed
+      consume(buf[d], k0 + d, std::false_type());
+      refill(d, k0 + d + DEPTH);
     }
   }
-  for (; k0 < nr; k0 += DEPTH) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      const int64_t k = k0 + d;
-      if (k < nr) {
-        consume(buf[d], k);
-        const int64_t kn = k + DEPTH;
-        if (kn < nr) {
-#pragma unroll
-          for (int u = 0; u < U; ++u) buf[d][u] = ld_stream(vp + (kn * U + u) * BD + t);
-        }
-      }
-    }
-  }
+  for (int d = 0; d < DEPTH; ++d)
+    if (k0 + d < nt) consume(buf[d], k0 + d, std::true_type());
 }
 
 // ----------------------------------------------------------------------------- streaming row state
@@ -376,21 +381,16 @@ struct NormState {
   float T = 0.f;
 };
 
-template <int N, bool GUARD, bool WITH_T>
-__device__ __forceinline__ void norm_chunk(NormState& s, const float* f, uint32_t valid, float cmax) {
+template <int N, bool WITH_T>
+__device__ __forceinline__ void norm_chunk(NormState& s, const float* f, float cmax) {
   const float ms_new = fmaxf(s.ms, cmax * kLog2e);
   const float d = s.ms - ms_new;
   const float sc = fexp2(d);
   float cs = 0.f, ct = 0.f;
 #pragma unroll
   for (int j = 0; j < N; ++j) {
-    float x = fmaf(f[j], kLog2e, -ms_new);
-    float e = fexp2(x);
-    if (GUARD) {
-      const bool ok = (valid >> j) & 1u;
-      e = ok ? e : 0.f;
-      x = ok ? x : 0.f;
-    }
+    const float x = fmaf(f[j], kLog2e, -ms_new);
+    const float e = fexp2(x);
     cs += e;
     if (WITH_T) ct = fmaf(e, x, ct);
   }
@@ -444,20 +444,23 @@ __device__ __forceinline__ void var_chunk(ConfState& s, const float* f, uint32_t
   s.vn = n1;
 }
 
-template <int N, bool GUARD, bool VAR>
+template <int N, bool VAR>
 __device__ __forceinline__ void conf_chunk(ConfState& s, const float* f, uint32_t valid, int cid) {
   const float cmax = chunk_max<N>(f);
   s.gid = cmax > s.t1 ? cid : s.gid;
   s.t2 = __builtin_amdgcn_fmed3f(s.t1, s.t2, cmax);
   s.t1 = fmaxf(s.t1, cmax);
-  norm_chunk<N, GUARD, true>(s.n, f, valid, cmax);
-  if (VAR) var_chunk<N, GUARD>(s, f, valid);
+  norm_chunk<N, true>(s.n, f, cmax);
+  if constexpr (VAR) {
+    if (N == 1 || __ballot(valid != 0xffffffffu) == 0ull) var_chunk<N, false>(s, f, valid);
+    else var_chunk<N, true>(s, f, valid);
+  }
 }
 
 template <bool VAR>
 __device__ __forceinline__ void conf_one(ConfState& s, float z, int cid) {
   float f[1] = {z};
-  conf_chunk<1, false, VAR>(s, f, 1u, cid);
+  conf_chunk<1, VAR>(s, f, 1u, cid);
 }
 
 // For a thread holding the row max `m`: the lowest index holding it in its chunk `cid`
@@ -493,12 +496,7 @@ __device__ __forceinline__ void max_chunk(const T* row, const Geom& g, int64_t n
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      v[u].x = kept ? keep[u].x : v[u].x;
-      v[u].y = kept ? keep[u].y : v[u].y;
-      v[u].z = kept ? keep[u].z : v[u].z;
-      v[u].w = kept ? keep[u].w : v[u].w;
-    }
+    for (int u = 0; u < U; ++u) v[u] = select4(kept, keep[u], v[u]);
     int pos = -1;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -555,16 +553,16 @@ __device__ __forceinline__ cmsd_row_stats row_stats_record(float m, float z2, do
 }
 
 // One drafter row -> its stats record (and, with VAR, its logit variance), by one
-// workgroup of BD threads.  KEEP_WIDE keeps the max round's vectors in registers for
-// every workgroup size, not only 64-thread rows (the kernel's registers permitting).
+// workgroup of BD threads.  One-wave workgroups keep the max round's vectors in registers;
+// in wider ones the registers cost more waves per SIMD than the re-read costs time.
 #ifndef CMSD_KEEP_MAX_ROUND
 #define CMSD_KEEP_MAX_ROUND 1
 #endif
-template <typename T, int BD, bool VAR, int DEPTH = CMSD_STREAM_DEPTH, bool KEEP_WIDE = false>
+template <typename T, int BD, bool VAR, int DEPTH = CMSD_STREAM_DEPTH>
 __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, const ConfArgs& a,
                                          cmsd_row_stats* __restrict__ out, float* __restrict__ var_out) {
   using E = Elem<T>;
-  constexpr bool KEEP = CMSD_KEEP_MAX_ROUND && (BD == 64 || KEEP_WIDE);
+  constexpr bool KEEP = CMSD_KEEP_MAX_ROUND && BD == 64;
   constexpr int VEC = E::VEC, U = E::U, N = VEC * U;
   constexpr int ND = VAR ? 5 : 2;  // fp64 sums of the epilogue: A, T (+ count, S1, S2)
   __shared__ double sd[(VAR ? 3 : 1) * (BD / 64)];
@@ -577,7 +575,7 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
     const Geom g = row_geom(row, V);
     const uint4* vp = reinterpret_cast<const uint4*>(row + g.head);
     const int64_t per_round = (int64_t)U * BD;
-    const int64_t nr = g.nvec / per_round;
+    const int64_t nr = g.nvec / per_round, rb = nr * per_round;  // full rounds and their vectors
 
     ConfState s;
     // KEEP: the vectors of the round that set this thread's maximum stay in registers,
@@ -597,57 +595,47 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
       return fmaxf(z, kMaskedLogit);
     };
 
-    // full rounds, next round's loads issued before the current one is consumed
-    // the head elements are loaded and folded in once the first rounds are requested
-    stream_rounds<U, BD, DEPTH>(vp, nr, t, [&] {
-      if (t < g.head) conf_one<VAR>(s, clamp1(E::load(row + t)), 0);
-    }, [&](const uint4 (&raw)[U], int64_t k) {
+    // the head and tail elements are requested with the first rounds and folded in after
+    // the last one, the tail first (the head then wins a tie for the row max)
+    const int64_t tail0 = g.head + g.nvec * VEC;
+    float hv = 0.f, tv = 0.f;
+    stream_rounds<U, BD, DEPTH>(vp, g.nvec, t, [&] {
+      hv = E::load(row + (t < g.head ? t : 0));
+      tv = E::load(row + (t < g.tail ? tail0 + t : 0));
+    }, [&](uint4 (&raw)[U], int64_t k, auto last) {
+      // lanes of the partial round past the row: the probe sees zeros there, and the sums
+      // the clamp value, which adds exactly 0 to A and T as a masked logit does (the
+      // variance moments skip them)
+      uint32_t valid = 0xffffffffu;
+      if (last && k == nr) {
+        valid = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const bool in = rb + (int64_t)u * BD + t < g.nvec;
+          valid |= in ? ((1u << VEC) - 1u) << (u * VEC) : 0u;
+          probe.add(raw[u]);
+          raw[u] = select4(in, raw[u], E::raw_masked());
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) probe.add(raw[u]);
+      }
       float f[N];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        probe.add(raw[u]);
-        E::unpack(E::clamp_masked(raw[u]), f + u * VEC);
-      }
-      conf_chunk<N, false, VAR>(s, f, 0xffffffffu, int(k + 1));
+      for (int u = 0; u < U; ++u) E::unpack(E::clamp_masked(raw[u]), f + u * VEC);
+      conf_chunk<N, VAR>(s, f, valid, int(k + 1));
       if (KEEP) {
         const bool up = s.gid == int(k + 1);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          keep[u].x = up ? raw[u].x : keep[u].x;
-          keep[u].y = up ? raw[u].y : keep[u].y;
-          keep[u].z = up ? raw[u].z : keep[u].z;
-          keep[u].w = up ? raw[u].w : keep[u].w;
-        }
+        for (int u = 0; u < U; ++u) keep[u] = select4(up, raw[u], keep[u]);
       }
     });
-    // partial round: whole vectors clamped and probed as in the full rounds; lanes past
-    // the row show the probe zeros and hold the clamp value, which adds exactly 0 to A
-    // and T as a masked logit does, so the round takes the unguarded arithmetic (the
-    // variance moments, which must not see padding, keep the guarded form and -inf)
-    const int64_t rb = nr * per_round;
-    if (rb < g.nvec) {
-      float f[N];
-      uint32_t valid = 0;
-      uint4 pv[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t j = rb + (int64_t)u * BD + t;
-        pv[u] = make_uint4(0u, 0u, 0u, 0u);
-        if (j < g.nvec) {
-          pv[u] = ld_stream(vp + j);
-          valid |= ((1u << VEC) - 1u) << (u * VEC);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        probe.add(pv[u]);
-        const bool in = (valid >> (u * VEC)) & 1u;
-        E::unpack(in ? E::clamp_masked(pv[u]) : (VAR ? E::raw_ninf() : E::raw_masked()), f + u * VEC);
-      }
-      conf_chunk<N, VAR, VAR>(s, f, valid, int(nr + 1));
+    if (t < g.tail) conf_one<VAR>(s, clamp1(tv), int(nr + 2));
+    if (t < g.head) {
+      const bool first = fmaxf(hv, kMaskedLogit) >= s.t1;
+      conf_one<VAR>(s, clamp1(hv), 0);
+      s.gid = first ? 0 : s.gid;
     }
-    const int64_t tail0 = g.head + g.nvec * VEC;
-    if (t < g.tail) conf_one<VAR>(s, clamp1(E::load(row + tail0 + t)), int(nr + 2));
 
     // ---- epilogue: row max, first index of the max, second logit, normaliser
     const float m = block_all_f<BD>(s.t1, OpMax(), sf);
@@ -659,7 +647,7 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
     const bool is_max = s.t1 == m;
     int64_t idx = INT64_MAX;
     float other = -INFINITY;
-    if (is_max) max_chunk<T, BD>(row, g, nr, s.gid, m, KEEP && s.gid <= nr, keep, idx, other);
+    if (is_max) max_chunk<T, BD>(row, g, nr, s.gid, m, KEEP, keep, idx, other);
     const float contrib = is_max ? s.t2 : s.t1;
     const int idx32 = idx == INT64_MAX ? INT32_MAX : int(idx);
 
@@ -773,8 +761,23 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
   }
 }
 
+// Waves per SIMD of a row kernel (0: as its registers come out).  A launch whose rows are
+// all in flight at once wants as many as fit, or its last rows run alone in a second
+// generation: 1088 bf16 rows of 256 threads, in flight together from 5 up, take 22.5 us at
+// 6 against 23.2 at 4 (V = 50257) and 54.7 against 56 (V = 152064); 512 drafter rows of
+// 128256 26.0 at 6 against 27.3 at 4.  A long launch streams best with few (more rows at a
+// time spread the reads over more of the memory): 8448 rows of 128256 in us, bf16 316.4 at
+// 2, 313.0 at 3, 314.7 at 4, 327 at 5; fp32 635 at 1, 617 at 2, 622.7 at 3, 627 at 4; 8192
+// bf16 drafter rows of 32000 88.0 at 2, 86.1 at 3, 86.7 at 4.
+#define CMSD_WAVES(W) __attribute__((amdgpu_waves_per_eu((W) ? (W) : 1, (W) ? (W) : 8)))
 template <typename T, int BD, bool VAR, int DEPTH>
-__global__ __launch_bounds__(BD) void k_confidence(const T* __restrict__ logits, int64_t n_rows, int64_t V,
+constexpr int kConfWaves = !std::is_same<T, Bf16>::value || VAR ? 0
+                           : DEPTH == 2 ? (BD == 256 ? 6 : 0) : (BD == 64 ? 3 : 0);
+template <typename T, int BD, int DEPTH>
+constexpr int kRowWaves = BD == 64 ? 0 : std::is_same<T, Bf16>::value ? (DEPTH == 2 ? 6 : 3) : (DEPTH == 2 ? 5 : 2);
+
+template <typename T, int BD, bool VAR, int DEPTH>
+__global__ __launch_bounds__(BD) CMSD_WAVES((kConfWaves<T, BD, VAR, DEPTH>)) void k_confidence(const T* __restrict__ logits, int64_t n_rows, int64_t V,
                                                    int64_t stride, ConfArgs a, cmsd_row_stats* __restrict__ out,
                                                    float* __restrict__ var_out) {
   const int64_t r = blockIdx.x;
@@ -914,19 +917,22 @@ struct TargetState {
   int gid = -1;  // first chunk (this thread's index order) attaining t1
 };
 
-template <int N, bool GUARD>
-__device__ __forceinline__ void target_chunk(TargetState& s, const float* f, uint32_t valid, int cid, bool count,
-                                             float gz, int beta, int& wcnt) {
+template <int N>
+__device__ __forceinline__ void target_chunk(TargetState& s, const float* f, int cid, bool count, float gz, int beta,
+                                             int& wcnt) {
   const float cmax = chunk_max<N>(f);
   s.gid = cmax > s.t1 ? cid : s.gid;
   s.t1 = fmaxf(s.t1, cmax);
-  norm_chunk<N, GUARD, false>(s.n, f, valid, cmax);
   // wave-uniform: count only when the gate needs it, skip chunks where no lane holds
   // a logit above the drafted one, and stop once this wave alone has seen top_beta
   if (count && wcnt < beta && __ballot(cmax > gz) != 0ull) {
 #pragma unroll
     for (int j = 0; j < N; ++j) wcnt += __popcll(__ballot(f[j] > gz));
   }
+  norm_chunk<N, false>(s.n, f, cmax);
+  // keeps the sums of this chunk from sinking below the next one's branch, which had both
+  // rounds' logits in registers at once (108 -> 65 for 256-thread bf16 rows)
+  asm volatile("" : "+v"(s.n.A), "+v"(s.n.ms));
 }
 
 // The target row pass.  prep() resolves the drafted token (and with it `count` and
@@ -940,44 +946,32 @@ __device__ __forceinline__ void target_stream(const T* row, const Geom& g, const
   const uint4* vp = reinterpret_cast<const uint4*>(row + g.head);
   const int64_t per_round = (int64_t)U * BD;
   const int64_t nr = g.nvec / per_round;
+  // the head and tail elements are requested with the first rounds (every lane loads, lanes
+  // past them element 0); the head is folded in once prep() has waited for its own loads
+  const int64_t tail0 = g.head + g.nvec * VEC;
+  float tv = 0.f;
   stream_rounds<U, BD, DEPTH>(
-      vp, nr, t,
+      vp, g.nvec, t,
       [&] {
-        // the head element is requested with the rounds, before prep() waits for
-        // its own loads (every lane loads, lanes past the head element 0)
         const float hv = E::load(row + (t < g.head ? t : 0));
+        tv = E::load(row + (t < g.tail ? tail0 + t : 0));
         prep();
         float f[1] = {t < g.head ? hv : -INFINITY};
-        target_chunk<1, true>(s, f, t < g.head ? 1u : 0u, 0, count, gz, beta, wcnt);
+        target_chunk<1>(s, f, 0, count, gz, beta, wcnt);
       },
-      [&](const uint4 (&raw)[U], int64_t k) {
+      [&](uint4 (&raw)[U], int64_t k, auto last) {
+        if (last && k == nr) {  // the partial round: -inf past the row
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            raw[u] = select4(nr * per_round + (int64_t)u * BD + t < g.nvec, raw[u], E::raw_ninf());
+        }
         float f[N];
 #pragma unroll
         for (int u = 0; u < U; ++u) E::unpack(raw[u], f + u * VEC);
-        target_chunk<N, false>(s, f, 0xffffffffu, int(k + 1), count, gz, beta, wcnt);
+        target_chunk<N>(s, f, int(k + 1), count, gz, beta, wcnt);
       });
-  const int64_t rb = nr * per_round;
-  if (rb < g.nvec) {
-    float f[N];
-    uint32_t valid = 0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t j = rb + (int64_t)u * BD + t;
-      if (j < g.nvec) {
-        E::unpack(ld_stream(vp + j), f + u * VEC);
-        valid |= ((1u << VEC) - 1u) << (u * VEC);
-      } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) f[u * VEC + e] = -INFINITY;
-      }
-    }
-    target_chunk<N, true>(s, f, valid, int(nr + 1), count, gz, beta, wcnt);
-  }
-  {
-    const int64_t tail0 = g.head + g.nvec * VEC;
-    float f[1] = {t < g.tail ? E::load(row + tail0 + t) : -INFINITY};
-    target_chunk<1, true>(s, f, t < g.tail ? 1u : 0u, int(nr + 2), count, gz, beta, wcnt);
-  }
+  float f[1] = {t < g.tail ? tv : -INFINITY};
+  target_chunk<1>(s, f, int(nr + 2), count, gz, beta, wcnt);
 }
 
 // The accept test of one drafted position y: standard speculative sampling
@@ -1139,21 +1133,14 @@ __global__ __launch_bounds__(BD) void k_target_rows(VerifyArgs a) {
 }
 
 // The row pass of cmsd_logit_pass: drafter rows (stats) and dense target rows in one
-// grid, drafter rows first; the two kinds of row do not depend on each other.  Its
-// bf16 drafter rows keep their max round in registers at every workgroup size when two
-// rounds are in flight: 118 instead of 115 registers at 256 threads, still 4 waves per
-// SIMD, and no re-read of that round before the record (64 sequences of 8 drafts: at
-// V = 50257, 43.2 -> 42.6 us per step; at V = 152064, 78.3 -> 77.8).  Three rounds in
-// flight, or fp32's 8-vector rounds, would lose a wave per SIMD.
-template <typename T, int DEPTH>
-constexpr bool kKeepWide = std::is_same<T, Bf16>::value && DEPTH == 2;
+// grid, drafter rows first; the two kinds of row do not depend on each other.
 template <typename T, int BD, int DEPTH>
-__global__ __launch_bounds__(BD) void k_row_pass(VerifyArgs a) {
+__global__ __launch_bounds__(BD) CMSD_WAVES((kRowWaves<T, BD, DEPTH>)) void k_row_pass(VerifyArgs a) {
   const int64_t nd = (int64_t)a.B * a.k_max;
   const int64_t r = blockIdx.x;
   if (r < nd)
-    conf_row<T, BD, false, DEPTH, kKeepWide<T, DEPTH>>(reinterpret_cast<const T*>(a.draft) + r * a.dstride, a.V,
-                                                         a.ca, a.dstats_out + r, nullptr);
+    conf_row<T, BD, false, DEPTH>(reinterpret_cast<const T*>(a.draft) + r * a.dstride, a.V, a.ca, a.dstats_out + r,
+                                  nullptr);
   else
     target_row<T, BD, true, DEPTH>(a, r - nd);
 }
@@ -1871,7 +1858,7 @@ __global__ __launch_bounds__(kFusedBD) void k_fused_pass(VerifyArgs a, int S, Sl
   const int64_t r = blockIdx.x;
   int b;
   if (r < nd) {
-    conf_row<T, kFusedBD, false, CMSD_STREAM_DEPTH, kKeepWide<T, CMSD_STREAM_DEPTH>>(
+    conf_row<T, kFusedBD, false>(
         reinterpret_cast<const T*>(a.draft) + r * a.dstride, a.V, a.ca, a.dstats_out + r, nullptr);
     b = int(r / a.k_max);
   } else {

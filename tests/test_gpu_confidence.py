@@ -110,6 +110,40 @@ def test_rounds_across_the_ring(cm, row_shape, block, dtype, depth):
         t.assert_ok()
 
 
+@pytest.mark.parametrize("depth", [2, 3])
+@pytest.mark.parametrize("block", [64, 256])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_round_edges_between_nans(cm, row_shape, block, dtype, depth):
+    # rows whose vectors end on, one before and one after the edge of a round, for every
+    # count of rounds the ring can be left with, between NaNs: nothing past a row's ends
+    # may reach its record (one NaN would make its sums NaN)
+    row_shape(block, depth)
+    lam = (0.2, 0.5, 0.3)
+    lam32 = tuple(Hn.f32(x) for x in lam)
+    vec = 4 if dtype == "f32" else 8
+    for nr in range(0, 2 * depth + 2):
+        for edge in (-1, 0, 1):
+            V = 32 * block * nr + vec * edge + (1 if nr % 2 else 0)     # odd: a tail element
+            if V < 2:
+                continue
+            g = np.random.default_rng(nr * 10 + edge + block)
+            rows = np.stack([g.normal(0, 2, V), g.normal(0, 0.1, V) - 50.0]).astype(np.float32)
+            buf32 = np.full((2, V + 16), np.nan, dtype=np.float32)
+            for head in (0, 5):                                        # aligned, and with a head
+                buf32[:] = np.nan
+                buf32[:, head:head + V] = rows
+                buf = buf32 if dtype == "f32" else W.bf16_bits_from_f32(buf32)
+                tdev = Hn.to_device(buf, dtype, torch.device("cuda:0"))[:, head:head + V]
+                st = cm.cmsd_confidence(tdev, lambdas=lam, beta_margin=0.7)
+                torch.cuda.synchronize()
+                gs = Hn.stats_np(st)
+                t = Hn.Tally()
+                for r in range(2):
+                    Hn.check_row_stats(t, gs, r, Hn.decode(np.ascontiguousarray(buf[r, head:head + V]), dtype), V,
+                                       lam32, Hn.f32(0.7))
+                t.assert_ok()
+
+
 def _sample_rows(cfg, k):
     n = cfg.draft_rows
     if n <= k:
