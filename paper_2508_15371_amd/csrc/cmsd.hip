@@ -202,6 +202,24 @@ __device__ __forceinline__ uint4 select4(bool c, const uint4& a, const uint4& b)
   return make_uint4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
 }
 
+// ----------------------------------------------------------------------------- hand-off inside a launch
+// Data that one workgroup leaves for another of the same launch.  Relaxed atomics at agent
+// scope go past the XCD's own L2, on both sides, so nothing has to be written back or
+// invalidated: the writer's stores have reached the point that every XCD sees once they
+// are acknowledged (the wait), and only then is its workgroup counted; the reader loads
+// after the count's return.  A device fence instead writes back the whole L2, 30 to 50 ns
+// of the chip per workgroup.
+__device__ __forceinline__ void st_agent(double* p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double ld_agent(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ int count_agent(int* p) {
+  return __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ----------------------------------------------------------------------------- wave / block reductions
 // Wave64 all-reduce: DPP quad permutes and row mirrors inside each 16-lane row,
 // then the four row results are combined through readlane (uniform result).
@@ -893,7 +911,8 @@ struct VerifyArgs {
 struct PassSlot {
   double A;       // sum 2^(z log2e - m log2e) of the row
   float m;        // row max
-  float gz, zd;   // target and drafter logits of the drafted token
+  float gz, zd;   // target and drafter logits of the drafted token; in the slot past the last
+                  // draft, zd's bits count the sequence's finished final-token workgroups
   int32_t ngt;    // logits above gz seen (wave counts stop once one reaches top_beta)
   int32_t top1;   // lowest index of the row max (GREEDY mode), else -1
   int32_t st;     // 1 drafted position, -1 the row after the last draft, -2 invalid drafted id
@@ -908,7 +927,7 @@ struct RowSlot {
   int32_t r;
   int32_t top1;  // lowest index of the row max (GREEDY mode), else -1
   float dm, dA;  // the drafter row's max and normaliser at this position (drafted positions)
-  int32_t pad;
+  int32_t done;  // position 0: final-token workgroups of the sequence that have finished
 };
 
 struct TargetState {
@@ -1106,7 +1125,8 @@ __device__ __forceinline__ void target_row(const VerifyArgs& a, int64_t q) {
     }
   }
   if (t == 0 && PASS) {
-    a.pslots[r] = PassSlot{A, m, gz, zd, ngt, top1, !valid ? -2 : (has_draft ? 1 : -1)};
+    // the slot past the last draft has no drafted token: its zd starts the final-token count
+    a.pslots[r] = PassSlot{A, m, gz, in_k ? zd : 0.f, ngt, top1, !valid ? -2 : (has_draft ? 1 : -1)};
   } else if (t == 0) {
     cmsd_target_stats res{};
     res.max_logit = m;
@@ -1310,11 +1330,10 @@ __device__ __forceinline__ SeqInfo seq_info(const VerifyArgs& a, int b, SeqInfo*
 
 // seq_info of the single-call pass: wave 0 reads the sequence's row results, drafter
 // stats, drafted ids and uniforms (one round trip, k_max < 64) and forms the draft
-// length and every accept test (as the separate calls would); with WRITE it also stores
+// length and every accept test (as the separate calls would); with `write` it also stores
 // the draft length and the target-row records.  The slots are only read, so every
 // workgroup of the final-token kernels forms the same decisions from them.
-template <bool WRITE>
-__device__ __forceinline__ SeqInfo seq_info_pass(const VerifyArgs& a, int b, SeqInfo* lds) {
+__device__ __forceinline__ SeqInfo seq_info_pass(const VerifyArgs& a, int b, bool write, SeqInfo* lds) {
   const int t = threadIdx.x, lane = t & 63;
   if (t < 64) {
     const int K = a.k_max;
@@ -1358,8 +1377,8 @@ __device__ __forceinline__ SeqInfo seq_info_pass(const VerifyArgs& a, int b, Seq
       q.msd = rl_f(dmx, c) * kLog2e;
       q.rho0 = (float)((double)(float)rl_d(sl.A, c) / (double)rl_f(dA, c));  // as from the verify slots
     }
-    if (WRITE && lane == 0) a.klen_out[b] = kb;
-    if (WRITE && lane <= K) {
+    if (write && lane == 0) a.klen_out[b] = kb;
+    if (write && lane <= K) {
       cmsd_target_stats res{};
       res.max_logit = sl.m;
       res.sum_exp = (float)sl.A;
@@ -1383,10 +1402,10 @@ __device__ __forceinline__ SeqInfo seq_info_pass(const VerifyArgs& a, int b, Seq
   return r;
 }
 
-// Where the final-token kernels of cmsd_logit_pass find their sequence's decisions:
-// in a record that k_pass_decide wrote (large launches), or formed by each of their
-// workgroups from the row slots (small launches: one launch fewer).  Verify is the
-// separate cmsd_verify, whose decisions come from its own row slots (seq_info).
+// Where the final-token kernels find their sequence's decisions: cmsd_logit_pass in a
+// record that k_pass_decide wrote (Record: k_final_parts and k_final_sample), or formed by
+// each workgroup from the row slots (Inline: k_final); cmsd_verify in its own row slots,
+// whose decisions are made (Verify: any of them).
 enum class Src { Verify, Record, Inline };
 
 // The sequence record of the single-call pass sits over the first two row slots of the
@@ -1405,7 +1424,7 @@ __global__ __launch_bounds__(64) void k_pass_decide(VerifyArgs a) {
   __shared__ SeqInfo s_q;
   const int b = blockIdx.x;
   if (b >= a.B) return;
-  const SeqInfo q = seq_info_pass<true>(a, b, &s_q);
+  const SeqInfo q = seq_info_pass(a, b, true, &s_q);
   if (threadIdx.x == 0) {
     *pass_info(a, b) = q;
     if (q.nacc < 0) {
@@ -1478,9 +1497,7 @@ __global__ __launch_bounds__(kPartBD) void k_final_parts(VerifyArgs a, int S, in
   const int t = threadIdx.x;
   const int b = blockIdx.x / SW, sl0 = (blockIdx.x % SW) * kSubPerWG;
   if (b >= a.B) return;
-  const SeqInfo q = SRC == Src::Record   ? *pass_info(a, b)
-                    : SRC == Src::Inline ? seq_info_pass<false>(a, b, &s_q)
-                                         : seq_info(a, b, &s_q);
+  const SeqInfo q = SRC == Src::Record ? *pass_info(a, b) : seq_info(a, b, &s_q);
   if (q.nacc < 0) return;
   const bool resid = q.nacc < q.kb;
   const T* trow = reinterpret_cast<const T*>(a.target) + q.tr * a.tstride;
@@ -1647,34 +1664,46 @@ __device__ __forceinline__ int locate_units(const T* trow, const T* drow, const 
 }
 
 // Inverse-CDF sample over one row (RESID off) or the residual of a row pair, from
-// the row's vocabulary-slice partials P[0..S): rho = sum e_t / sum e_d (fresh sums),
-// slice masses corrected to first order in rho - rho0 and scanned in slice order
-// (each thread a contiguous run of slices, its first partial kept in registers),
-// then an exact scan/locate inside the chosen slice.  A zero residual falls back to
-// the target row.  Run by one workgroup of BD threads; s_sc holds 3 doubles, sd
+// the row's S vocabulary-slice partials, part(s) loading slice s: rho = sum e_t / sum e_d
+// (fresh sums), slice masses corrected to first order in rho - rho0 and scanned in slice
+// order (each thread a contiguous run of slices, its first kRunRegs partials kept in
+// registers), then an exact scan/locate inside the chosen slice.  A zero residual falls
+// back to the target row.  Run by one workgroup of BD threads; s_sc holds 3 doubles, sd
 // 2*BD/64 and si BD/64.
-template <typename T, int BD>
+template <typename T, int BD, typename PF>
 __device__ __forceinline__ int sample_from_parts(const T* trow, const T* drow, int64_t V, bool resid, float mst, float msd,
-                                 float rho0, float u, const SlicePart* __restrict__ P, int S, double* sd, int* si,
-                                 double* s_sc, int* s_y, const SlicePart* first = nullptr) {
+                                 float rho0, float u, int S, double* sd, int* si,
+                                 double* s_sc, int* s_y, PF&& part) {
+  constexpr int kRunRegs = BD >= 256 ? 1 : 256 / BD;
   const int t = threadIdx.x;
   const bool same_phase = ((reinterpret_cast<uintptr_t>(trow) ^ reinterpret_cast<uintptr_t>(drow)) & 15u) == 0;
   const int slo = (int)((int64_t)t * S / BD), shi = (int)((int64_t)(t + 1) * S / BD);
-  // `first`: this thread's first partial, already loaded by the caller
-  const SlicePart p0 = first ? *first : (slo < shi ? P[slo] : SlicePart{0.0, 0.0, 0.0, 0.0});
+  SlicePart run[kRunRegs];
+#pragma unroll
+  for (int j = 0; j < kRunRegs; ++j) run[j] = slo + j < shi ? part(slo + j) : SlicePart{0.0, 0.0, 0.0, 0.0};
+  // every partial of the run in slice order; f returns whether to go on
+  auto each = [&](auto&& f) {
+    bool on = true;
+#pragma unroll
+    for (int j = 0; j < kRunRegs; ++j)
+      if (on && slo + j < shi) on = f(slo + j, run[j]);
+    for (int s = slo + kRunRegs; on && s < shi; ++s) on = f(s, part(s));
+  };
   // fresh normalisers and the exact ratio
   double tot[2] = {0.0, 0.0};
-  for (int s = slo; s < shi; ++s) {
-    const SlicePart p = s == slo ? p0 : P[s];
+  each([&](int, const SlicePart& p) {
     tot[0] += p.et;
     tot[1] += p.ed;
+    return true;
+  });
+  double rho = 0.0;
+  if (resid) {
+    block_sum_n<BD, 2>(tot, sd);
+    rho = tot[0] / tot[1];
   }
-  block_sum_n<BD, 2>(tot, sd);
-  const double rho = resid ? tot[0] / tot[1] : 0.0;
   // slice masses (first-order correction of the rho0 sums); a zero residual falls
   // back to the target row itself
-  auto mass = [&](int s, bool rs) -> double {
-    const SlicePart p = s == slo ? p0 : P[s];
+  auto mass = [&](const SlicePart& p, bool rs) -> double {
     if (!rs) return p.et;
     const double m = p.q - (rho - (double)rho0) * p.qd;
     return m > 0.0 ? m : 0.0;
@@ -1684,7 +1713,10 @@ __device__ __forceinline__ int sample_from_parts(const T* trow, const T* drow, i
   const int64_t nu = g.nvec + 2;
   for (int pass = 0; pass < 2 && y < 0; ++pass) {
     double sm = 0.0;
-    for (int s = slo; s < shi; ++s) sm += mass(s, resid);
+    each([&](int, const SlicePart& p) {
+      sm += mass(p, resid);
+      return true;
+    });
     const double excl = block_excl_scan<BD>(sm, sd);
     const double end = excl + sm;
     const int tlast = block_all_i<BD>(sm > 0.0 ? t : -1, OpMaxI(), si);
@@ -1701,16 +1733,17 @@ __device__ __forceinline__ int sample_from_parts(const T* trow, const T* drow, i
       // the slice inside this thread's run, repeating its sequential sums exactly
       double Pacc = 0.0, sbase = 0.0;
       int sstar = -1;
-      for (int s = slo; s < shi; ++s) {
-        const double m = mass(s, resid);
+      each([&](int s, const SlicePart& p) {
+        const double m = mass(p, resid);
         const double Pn = Pacc + m;
         if (m > 0.0) {
           sstar = s;
           sbase = excl + Pacc;
-          if (tp != INT32_MAX && excl + Pn > x) break;
+          if (tp != INT32_MAX && excl + Pn > x) return false;
         }
         Pacc = Pn;
-      }
+        return true;
+      });
       s_sc[0] = sbase;
       s_sc[2] = (double)sstar;
     }
@@ -1747,9 +1780,7 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
   // and in GREEDY mode, where no partials were written; always inside the workspace)
   const int slo = (int)((int64_t)t * S / BD), shi = (int)((int64_t)(t + 1) * S / BD);
   const SlicePart first = slo < shi ? ws[(int64_t)b * S + slo] : SlicePart{0.0, 0.0, 0.0, 0.0};
-  const SeqInfo q = SRC == Src::Record   ? *pass_info(a, b)
-                    : SRC == Src::Inline ? seq_info_pass<true>(a, b, &s_q)
-                                         : seq_info(a, b, &s_q);
+  const SeqInfo q = SRC == Src::Record ? *pass_info(a, b) : seq_info(a, b, &s_q);
   if (SRC == Src::Record && (q.nacc < 0 || a.mode == CMSD_MODE_GREEDY)) return;  // written by k_pass_decide
   if (q.nacc < 0) {
     if (t == 0) {
@@ -1770,12 +1801,86 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
   const T* trow = reinterpret_cast<const T*>(a.target) + q.tr * a.tstride;
   const T* drow = reinterpret_cast<const T*>(a.draft) + q.dr * a.dstride;
   const float u = a.unif[q.off + q.kb];
-  const int y = sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, ws + (int64_t)b * S, S, sd,
-                                     si, s_sc, &s_y, &first);
+  const int y = sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, sd, si, s_sc, &s_y,
+                                         [&](int s) { return s == slo ? first : ws[(int64_t)b * S + s]; });
   if (t == 0) {
     a.n_acc[b] = nacc;
     a.next_tok[b] = y;
   }
+}
+
+// Both in one launch, for small launches: SW workgroups of kFinalWaves waves per sequence.
+// Each forms the sequence's decisions, each of its waves sums one slice of the chosen row
+// (pair) and leaves the partials, and the workgroup that counts last samples from them (in
+// k_final_sample's order, so the outputs are the same bits).  The row pass before set the
+// count to zero.  Workgroup 0 of a sequence also writes what the decisions decide.  Bound
+// by its chain of memory round trips; us, MI355X, against the pair (V, sequences, bf16):
+// 32000 x 1 12.4 -> 10.0, 32000 x 8 13.5 -> 10.7, 50257 x 64 18.4 -> 16.0, 152064 x 64 (19
+// slice waves per compute unit) 23.4 -> 23.3; then the counting and the waits of resident
+// workgroups cost more than a launch: 32000 x 512 (32 per unit) 24.5 -> 31, 128256 x 256
+// (63 per unit) 37 -> 49.  Workgroups of 1, 2, 4 and 8 waves: 11.3, 10.6, 10.0 and 11.9 at
+// 32000 x 1, 18.3, 17.2, 16.0 and 15.9 at 50257 x 64.
+constexpr int kFinalWaves = 4;
+constexpr int kFinalBD = 64 * kFinalWaves;
+template <Src SRC>
+__device__ __forceinline__ int* final_count(const VerifyArgs& a, int b) {
+  if (SRC == Src::Verify) return &a.slots[(int64_t)b * (a.k_max + 1)].done;
+  return reinterpret_cast<int*>(&a.pslots[(int64_t)b * (a.k_max + 1) + a.k_max].zd);
+}
+
+template <typename T, Src SRC>
+__global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW, SlicePart* __restrict__ ws) {
+  constexpr int BD = kFinalBD;
+  __shared__ double sd[2 * kFinalWaves];
+  __shared__ int si[kFinalWaves];
+  __shared__ double s_sc[3];
+  __shared__ int s_y;
+  __shared__ SeqInfo s_q;
+  const int t = threadIdx.x;
+  const int b = int(blockIdx.x / (unsigned)SW), part = int(blockIdx.x % (unsigned)SW);
+  if (b >= a.B) return;
+  const SeqInfo q = SRC == Src::Inline ? seq_info_pass(a, b, part == 0, &s_q) : seq_info(a, b, &s_q);
+  if (part == 0 && t == 0) {
+    a.n_acc[b] = q.nacc;
+    if (q.nacc < 0) a.next_tok[b] = -1;
+  }
+  if (q.nacc < 0) return;
+  const bool resid = q.nacc < q.kb;
+  const T* trow = reinterpret_cast<const T*>(a.target) + q.tr * a.tstride;
+  const T* drow = reinterpret_cast<const T*>(a.draft) + q.dr * a.dstride;
+  const bool same_phase = ((reinterpret_cast<uintptr_t>(trow) ^ reinterpret_cast<uintptr_t>(drow)) & 15u) == 0;
+  const Geom g = row_geom(trow, a.V);
+  SlicePart* P = ws + (int64_t)b * S;
+  const int sl = part * kFinalWaves + __builtin_amdgcn_readfirstlane(t >> 6);
+  if (sl < S) {
+    const int lane = t & 63;
+    double sum[1][4] = {};
+    const int64_t u_first = (int64_t)sl * kSliceUnits;
+    if (u_first < g.nvec + 2) {
+      if (resid)
+        parts_wave<T, true, 1>(trow, drow, g, same_phase, u_first, lane, q.mst, q.msd, q.rho0, sum);
+      else
+        parts_wave<T, false, 1>(trow, trow, g, true, u_first, lane, q.mst, 0.f, 0.f, sum);
+    }
+    double r = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const double w = wave_all_d(sum[0][j], OpSumD());
+      r = lane == j ? w : r;
+    }
+    if (lane < 4) st_agent(reinterpret_cast<double*>(P + sl) + lane, r);
+  }
+  wait_stores();  // every wave's partials, before its workgroup is counted
+  __syncthreads();
+  if (t == 0) si[0] = count_agent(final_count<SRC>(a, b));
+  __syncthreads();
+  if (si[0] != SW - 1) return;
+  const float u = a.unif[q.off + q.kb];
+  const int y = sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, sd, si, s_sc, &s_y, [&](int s) {
+    const double* p = reinterpret_cast<const double*>(P + s);
+    return SlicePart{ld_agent(p), ld_agent(p + 1), ld_agent(p + 2), ld_agent(p + 3)};
+  });
+  if (t == 0) a.next_tok[b] = y;
 }
 
 // ----------------------------------------------------------------------------- K5 draft sampling
@@ -1808,7 +1913,7 @@ __device__ __forceinline__ void fused_tail(const VerifyArgs& a, int b, int S, Sl
   __shared__ double s_sc[3];
   __shared__ int s_y;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const SeqInfo q = seq_info_pass<true>(a, b, &s_q);
+  const SeqInfo q = seq_info_pass(a, b, true, &s_q);
   if (q.nacc < 0 || a.mode == CMSD_MODE_GREEDY) {
     if (t == 0) {
       a.n_acc[b] = q.nacc < 0 ? -1 : q.nacc;
@@ -1843,7 +1948,8 @@ __device__ __forceinline__ void fused_tail(const VerifyArgs& a, int b, int S, Sl
   }
   __syncthreads();  // the partials of every slice, written by this workgroup
   const float u = a.unif[q.off + q.kb];
-  const int y = sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, P, S, sd, si, s_sc, &s_y);
+  const int y = sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, sd, si, s_sc, &s_y,
+                                         [&](int s) { return P[s]; });
   if (t == 0) {
     a.n_acc[b] = q.nacc;
     a.next_tok[b] = y;
@@ -1921,8 +2027,8 @@ __global__ __launch_bounds__(kSampleBD) void k_draft_pick(const T* __restrict__ 
   __shared__ int s_y;
   const int64_t r = blockIdx.x;
   const T* row = logits + r * stride;
-  const int y = sample_from_parts<T, kSampleBD>(row, row, V, false, stats[r].max_logit * kLog2e, 0.f, 0.f, unif[r], ws + r * S,
-                                     S, sd, si, s_sc, &s_y);
+  const int y = sample_from_parts<T, kSampleBD>(row, row, V, false, stats[r].max_logit * kLog2e, 0.f, 0.f, unif[r], S, sd, si,
+                                                s_sc, &s_y, [&](int s) { return ws[r * S + s]; });
   if (threadIdx.x == 0) out[r] = y;
 }
 
@@ -2179,61 +2285,75 @@ cmsd_status bind_pass_workspace(VerifyArgs& a, void* workspace, size_t workspace
   return CMSD_OK;
 }
 
-// The final-token pair of cmsd_logit_pass, its decisions found as SRC says.
+// The final-token launches of sampled modes: one (k_final) or the pair.
 template <typename T, Src SRC>
-void launch_final(const VerifyArgs& a, int S, int SW, SlicePart* ws, hipStream_t st) {
+void launch_final(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
+  const int SW = (S + kFinalWaves - 1) / kFinalWaves;
+  hipLaunchKernelGGL((k_final<T, SRC>), dim3((unsigned)(a.B * SW)), dim3(kFinalBD), 0, st, a, S, SW, ws);
+}
+template <typename T, Src SRC>
+void launch_final_pair(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
+  const int SW = (S + kSubPerWG - 1) / kSubPerWG;
   const unsigned gp = (unsigned)((int64_t)a.B * SW);
   hipLaunchKernelGGL((k_final_parts<T, SRC>), dim3(gp), dim3(kPartBD), 0, st, a, S, SW, ws);
   hipLaunchKernelGGL((k_final_sample<T, SRC>), dim3((unsigned)a.B), dim3(kSampleBD), 0, st, a, S, ws);
 }
 
-// Whether the final-token workgroups of cmsd_logit_pass form their sequence's decisions
-// themselves instead of reading k_pass_decide's record: up to 32 slice waves per compute
-// unit the launch saved outweighs the repeated decisions (8 or 64 sequences of 8 drafts
-// at V = 32000 to 152064); 256 sequences at V = 128256 (63 slices each: 63 waves per
-// unit) keep the decision kernel.
-// cmsd_set_pass_decisions forces either (0 = chosen per call, 1 = record, 2 = inline).
+// Whether the final token of a launch of that many slices takes one launch (k_final, which
+// in cmsd_logit_pass also forms the decisions) or, in cmsd_logit_pass behind the decision
+// kernel, two: up to 20 slice waves per compute unit one is faster or as fast (figures at
+// k_final).  cmsd_set_pass_decisions forces cmsd_logit_pass to either (0 = chosen per call,
+// 1 = record and pair, 2 = one launch); a grid past the launch limit takes the pair.
 std::atomic<int> g_pass_decisions{0};
+bool one_final_launch(int64_t batch, int S, int forced) {
+  if (!launch_fits(batch * ((S + kFinalWaves - 1) / kFinalWaves), kFinalBD)) return false;
+  if (forced) return forced == 2;
+  return batch * S <= 20 * (int64_t)device_cus();
+}
 
 // Timing events armed by cmsd_set_row_events for the next cmsd_logit_pass call of this
 // host thread (a measurement hook kept out of the call's own arguments).
 thread_local hipEvent_t t_row_events[2] = {nullptr, nullptr};
-bool inline_decisions(unsigned slice_waves) {
-  if (const int m = g_pass_decisions.load(std::memory_order_relaxed)) return m == 2;
-  return slice_waves <= 32u * (unsigned)device_cus();
-}
-
 // The launches of cmsd_logit_pass on a bound workspace: the joint row pass (bracketed
-// by the caller's events, if any), then either the final-token pair forming the
-// decisions in its workgroups (small launches), or the per-sequence decisions followed
-// by the final-token pair (not in GREEDY mode, whose final token is the row's top token).
+// by the caller's events, if any), then either one final-token launch that forms the
+// decisions too (small launches), or the per-sequence decisions followed by the
+// final-token pair (not in GREEDY mode, whose final token is the row's top token).
+template <typename T>
+void launch_pass_final(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
+  const bool greedy = a.mode == CMSD_MODE_GREEDY;
+  if (!greedy && one_final_launch(a.B, S, g_pass_decisions.load(std::memory_order_relaxed))) {
+    launch_final<T, Src::Inline>(a, S, ws, st);
+    return;
+  }
+  hipLaunchKernelGGL(k_pass_decide, dim3((unsigned)a.B), dim3(64), 0, st, a);
+  if (!greedy) launch_final_pair<T, Src::Record>(a, S, ws, st);
+}
 cmsd_status enqueue_logit_pass(const VerifyArgs& a, int32_t dtype, void* workspace, hipEvent_t e0, hipEvent_t e1,
                                hipStream_t st) {
   const int es = dtype == CMSD_F32 ? 4 : 2;
   const int64_t drows = (int64_t)a.B * a.k_max, trows = (int64_t)a.B * (a.k_max + 1);
   const int S = verify_slices(a.V, es);
-  const int SW = (S + kSubPerWG - 1) / kSubPerWG;
   SlicePart* ws = static_cast<SlicePart*>(workspace);
-  const unsigned gp = (unsigned)((int64_t)a.B * SW);
   const int bd = row_block(drows + trows, a.V * (int64_t)es);
-  if (dtype == CMSD_F32)
+  if (dtype == CMSD_F32) {
     launch_row_pass<float>(bd, a, drows + trows, st, e0, e1);
-  else
+    launch_pass_final<float>(a, S, ws, st);
+  } else {
     launch_row_pass<Bf16>(bd, a, drows + trows, st, e0, e1);
-  if (a.mode != CMSD_MODE_GREEDY && inline_decisions(gp)) {
-    if (dtype == CMSD_F32)
-      launch_final<float, Src::Inline>(a, S, SW, ws, st);
-    else
-      launch_final<Bf16, Src::Inline>(a, S, SW, ws, st);
-    return launched();
+    launch_pass_final<Bf16>(a, S, ws, st);
   }
-  hipLaunchKernelGGL(k_pass_decide, dim3((unsigned)a.B), dim3(64), 0, st, a);
-  if (a.mode == CMSD_MODE_GREEDY) return launched();
-  if (dtype == CMSD_F32)
-    launch_final<float, Src::Record>(a, S, SW, ws, st);
-  else
-    launch_final<Bf16, Src::Record>(a, S, SW, ws, st);
   return launched();
+}
+
+// The launches of cmsd_verify after its target rows (GREEDY: the outputs only).
+template <typename T>
+void launch_verify_final(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
+  if (a.mode == CMSD_MODE_GREEDY)
+    hipLaunchKernelGGL((k_final_sample<T, Src::Verify>), dim3((unsigned)a.B), dim3(kSampleBD), 0, st, a, S, ws);
+  else if (one_final_launch(a.B, S, 0))
+    launch_final<T, Src::Verify>(a, S, ws, st);
+  else
+    launch_final_pair<T, Src::Verify>(a, S, ws, st);
 }
 
 // ----------------------------------------------------------------------------- static scratch
@@ -2401,22 +2521,16 @@ cmsd_status cmsd_verify(const void* draft_logits, int64_t draft_stride, const cm
   a.next_tok = next_token;
   const hipStream_t st = as_stream(stream);
   const int S = verify_slices(vocab, (int)es);
-  const int SW = (S + kSubPerWG - 1) / kSubPerWG;
   SlicePart* ws = static_cast<SlicePart*>(workspace);
   a.slots = reinterpret_cast<RowSlot*>(ws + (size_t)batch * verify_slices(vocab, 4));
-  const unsigned gp = (unsigned)((int64_t)batch * SW);
   // the shape suits the scored rows; the grid covers every (sequence, position)
   const int bd = fit_block(row_block(target_rows, vocab * (int64_t)es), (int64_t)batch * (k_max + 1));
   if (dtype == CMSD_F32) {
     launch_target_rows<float>(bd, a, st);
-    if (a.mode != CMSD_MODE_GREEDY)
-      hipLaunchKernelGGL((k_final_parts<float, Src::Verify>), dim3(gp), dim3(kPartBD), 0, st, a, S, SW, ws);
-    hipLaunchKernelGGL((k_final_sample<float, Src::Verify>), dim3((unsigned)batch), dim3(kSampleBD), 0, st, a, S, ws);
+    launch_verify_final<float>(a, S, ws, st);
   } else {
     launch_target_rows<Bf16>(bd, a, st);
-    if (a.mode != CMSD_MODE_GREEDY)
-      hipLaunchKernelGGL((k_final_parts<Bf16, Src::Verify>), dim3(gp), dim3(kPartBD), 0, st, a, S, SW, ws);
-    hipLaunchKernelGGL((k_final_sample<Bf16, Src::Verify>), dim3((unsigned)batch), dim3(kSampleBD), 0, st, a, S, ws);
+    launch_verify_final<Bf16>(a, S, ws, st);
   }
   return launched();
 }
