@@ -1559,226 +1559,213 @@ __device__ __forceinline__ void unit_weights(const uint4& rt, const uint4& rd, f
   }
 }
 
-// Block exclusive scan of one double per thread (wave scan by shuffles, wave totals
-// added in order): deterministic.
-template <int BD>
-__device__ __forceinline__ double block_excl_scan(double v, double* sd) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  double incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double up = __shfl_up(incl, o);
-    if (lane >= o) incl += up;
-  }
-  double ex = __shfl_up(incl, 1);
-  if (lane == 0) ex = 0.0;
-  __syncthreads();
-  if (lane == 63) sd[w] = incl;
-  __syncthreads();
-  double pre = 0.0;
-  for (int i = 0; i < w; ++i) pre += sd[i];
-  return pre + ex;
+// Wave inclusive scan of one double per lane by DPP (row shifts inside each 16-lane row,
+// then the row totals broadcast forward): a fixed order, and a third of the time of a
+// shuffle scan's LDS round trips.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add_d(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, false);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_incl_scan(double v) {
+  v = dpp_add_d<0x111, 0xF>(v);  // row_shr:1
+  v = dpp_add_d<0x112, 0xF>(v);  // row_shr:2
+  v = dpp_add_d<0x114, 0xF>(v);  // row_shr:4
+  v = dpp_add_d<0x118, 0xF>(v);  // row_shr:8
+  v = dpp_add_d<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
+  v = dpp_add_d<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
+  return v;
 }
 
-// Units of one slice per thread of a BD-thread sampling workgroup (one each, and
-// none for the threads past the slice, when the workgroup is wider than a slice).
-template <int BD>
-constexpr int loc_upt() {
-  return BD >= kSliceUnits ? 1 : kSliceUnits / BD;
-}
-static_assert(kSliceUnits % kSampleBD == 0, "a slice splits evenly over the sampling workgroup");
-
-// Smallest element y in units [ulo, uhi) with q_y > 0 and base + C(y) > x, C the
-// cumulative weight from ulo in a fixed order: thread t owns the loc_upt<BD>() units
-// from ulo + t*loc_upt<BD>() (kept in registers) and sums them unit by unit, a block scan
-// orders the threads, and the thread whose span crosses x repeats its own sums
-// exactly.  If none qualifies, the last element with q_y > 0.  Returns -1 if every
-// weight is 0.  The result passes through *s_y.
-template <typename T, bool RESID, int BD>
-__device__ __forceinline__ int locate_units(const T* trow, const T* drow, const Geom& g, bool same_phase, int64_t ulo, int64_t uhi,
-                            float mst, float msd, double rho, double base, double x, double* sd, int* si,
-                            int* s_y) {
-  using E = Elem<T>;
-  constexpr int VEC = E::VEC, UPT = loc_upt<BD>();
-  const int t = threadIdx.x;
-  const int64_t u0 = ulo + (int64_t)t * UPT;
-  uint4 rt[UPT], rd[UPT];
-#pragma unroll
-  for (int j = 0; j < UPT; ++j) {
-    const bool in = u0 + j < uhi;
-    rt[j] = in ? unit_raw<T, false>(trow, g, u0 + j) : E::raw_ninf();
-    rd[j] = RESID && in ? unit_raw2<T, false>(drow, g, u0 + j, same_phase) : rt[j];
-  }
-  double us[UPT];
-  double s = 0.0;
-#pragma unroll
-  for (int j = 0; j < UPT; ++j) {
-    double q[VEC];
-    unit_weights<T, RESID>(rt[j], rd[j], mst, msd, rho, q);
-    double v = 0.0;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) v += q[e];
-    us[j] = v;
-    s += v;
-  }
-  const double excl = block_excl_scan<BD>(s, sd);
-  const double end = base + (excl + s);
-  int pick = block_all_i<BD>((s > 0.0 && end > x) ? t : INT32_MAX, OpMinI(), si);
-  bool last = false;
-  if (pick == INT32_MAX) {
-    pick = block_all_i<BD>(s > 0.0 ? t : -1, OpMaxI(), si);
-    if (pick < 0) return -1;
-    last = true;
-  }
-  if (t == pick) {
-    int y = -1;
-    double P = 0.0;
-    bool done = false;
-#pragma unroll
-    for (int j = 0; j < UPT; ++j) {
-      const double Pn = P + us[j];
-      if (!done && us[j] > 0.0 && (last || base + (excl + Pn) > x)) {
-        double q[VEC];
-        unit_weights<T, RESID>(rt[j], rd[j], mst, msd, rho, q);
-        const int64_t first = unit_first<T>(g, u0 + j);
-        double Q = 0.0;
-        bool found = false;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          Q += q[e];
-          if (!found && q[e] > 0.0 && (last || base + (excl + (P + Q)) > x)) {
-            y = int(first + e);
-            found = !last;
-          }
-        }
-        done = !last;
-      }
-      P = Pn;
-    }
-    *s_y = y;
-  }
-  __syncthreads();
-  const int y = *s_y;
-  __syncthreads();
-  return y;
-}
+// What the sampling workgroup shares.
+struct SampleLds {
+  double base, x, rho;         // mass before the chosen slice, the sought mass, sum e_t / sum e_d
+  double excl, pre;            // mass of the slice before the chosen lane's units, and before its unit
+  double us[kSliceUnits];      // unit sums of the slice
+  int slice, resid, unit, last;
+};
 
 // Inverse-CDF sample over one row (RESID off) or the residual of a row pair, from
 // the row's S vocabulary-slice partials, part(s) loading slice s: rho = sum e_t / sum e_d
 // (fresh sums), slice masses corrected to first order in rho - rho0 and scanned in slice
-// order (each thread a contiguous run of slices, its first kRunRegs partials kept in
-// registers), then an exact scan/locate inside the chosen slice.  A zero residual falls
-// back to the target row.  Run by one workgroup of BD threads; s_sc holds 3 doubles, sd
-// 2*BD/64 and si BD/64.
-template <typename T, int BD, typename PF>
-__device__ __forceinline__ int sample_from_parts(const T* trow, const T* drow, int64_t V, bool resid, float mst, float msd,
-                                 float rho0, float u, int S, double* sd, int* si,
-                                 double* s_sc, int* s_y, PF&& part) {
-  constexpr int kRunRegs = BD >= 256 ? 1 : 256 / BD;
+// order, then an exact search inside the chosen slice: the smallest element y with q_y > 0
+// and base + C(y) > x, C the slice's cumulative weight in a fixed order (if none
+// qualifies, the last element with q_y > 0).  A zero residual falls back to the target
+// row.  Writes *out, -1 if every weight is 0.  Run by one workgroup of BD threads: one wave
+// searches the slices (each lane a contiguous run, its first kRunRegs partials in
+// registers) and the unit sums, thread i weighs unit i of the slice, and the thread of the
+// chosen unit repeats its own sums exactly: three barriers, where searches by the whole
+// workgroup took a dozen (MI355X: k_final, 1 sequence of 32000 9.9 -> 8.9 us, 64 of 152064
+// 24.9 -> 21.1; k_final_sample, 256 of 128256 7.0 -> 5.4).
+template <typename T, bool RESID, int BD>
+__device__ __forceinline__ bool sample_slice(const T* trow, const T* drow, const Geom& g, bool same_phase, float mst,
+                                             float msd, SampleLds& L, int32_t* out) {
+  using E = Elem<T>;
+  constexpr int VEC = E::VEC, UPL = kSliceUnits / 64;
+  static_assert(kSliceUnits <= BD && kSliceUnits % 64 == 0, "one unit per thread");
   const int t = threadIdx.x;
-  const bool same_phase = ((reinterpret_cast<uintptr_t>(trow) ^ reinterpret_cast<uintptr_t>(drow)) & 15u) == 0;
-  const int slo = (int)((int64_t)t * S / BD), shi = (int)((int64_t)(t + 1) * S / BD);
-  SlicePart run[kRunRegs];
+  const double base = L.base, x = L.x;
+  const int64_t u0 = (int64_t)L.slice * kSliceUnits + t;
+  double q[VEC];
+  if (t < kSliceUnits) {
+    // units past the row's last one (nvec + 1) are empty
+    const uint4 rt = unit_raw<T, false>(trow, g, u0);
+    const uint4 rd = RESID ? unit_raw2<T, false>(drow, g, u0, same_phase) : rt;
+    unit_weights<T, RESID>(rt, rd, mst, msd, L.rho, q);
+    double v = 0.0;
 #pragma unroll
-  for (int j = 0; j < kRunRegs; ++j) run[j] = slo + j < shi ? part(slo + j) : SlicePart{0.0, 0.0, 0.0, 0.0};
-  // every partial of the run in slice order; f returns whether to go on
-  auto each = [&](auto&& f) {
-    bool on = true;
-#pragma unroll
-    for (int j = 0; j < kRunRegs; ++j)
-      if (on && slo + j < shi) on = f(slo + j, run[j]);
-    for (int s = slo + kRunRegs; on && s < shi; ++s) on = f(s, part(s));
-  };
-  // fresh normalisers and the exact ratio
-  double tot[2] = {0.0, 0.0};
-  each([&](int, const SlicePart& p) {
-    tot[0] += p.et;
-    tot[1] += p.ed;
-    return true;
-  });
-  double rho = 0.0;
-  if (resid) {
-    block_sum_n<BD, 2>(tot, sd);
-    rho = tot[0] / tot[1];
+    for (int e = 0; e < VEC; ++e) v += q[e];
+    L.us[t] = v;
   }
-  // slice masses (first-order correction of the rho0 sums); a zero residual falls
-  // back to the target row itself
-  auto mass = [&](const SlicePart& p, bool rs) -> double {
-    if (!rs) return p.et;
-    const double m = p.q - (rho - (double)rho0) * p.qd;
-    return m > 0.0 ? m : 0.0;
-  };
-  int y = -1;
-  const Geom g = row_geom(trow, V);
-  const int64_t nu = g.nvec + 2;
-  for (int pass = 0; pass < 2 && y < 0; ++pass) {
-    double sm = 0.0;
-    each([&](int, const SlicePart& p) {
-      sm += mass(p, resid);
-      return true;
-    });
-    const double excl = block_excl_scan<BD>(sm, sd);
-    const double end = excl + sm;
-    const int tlast = block_all_i<BD>(sm > 0.0 ? t : -1, OpMaxI(), si);
-    if (tlast < 0) {
-      resid = false;  // no residual mass: sample from the target row
-      continue;
+  __syncthreads();
+  if (t < 64) {
+    double us[UPL], s = 0.0;
+#pragma unroll
+    for (int j = 0; j < UPL; ++j) {
+      us[j] = L.us[t * UPL + j];
+      s += us[j];
     }
-    if (t == tlast) s_sc[1] = end;
-    __syncthreads();
-    const double x = (double)u * s_sc[1];
-    const int tp = block_all_i<BD>((sm > 0.0 && end > x) ? t : INT32_MAX, OpMinI(), si);
-    const int tq = tp == INT32_MAX ? tlast : tp;
-    if (t == tq) {
-      // the slice inside this thread's run, repeating its sequential sums exactly
-      double Pacc = 0.0, sbase = 0.0;
-      int sstar = -1;
-      each([&](int s, const SlicePart& p) {
-        const double m = mass(p, resid);
-        const double Pn = Pacc + m;
-        if (m > 0.0) {
-          sstar = s;
-          sbase = excl + Pacc;
-          if (tp != INT32_MAX && excl + Pn > x) return false;
+    const double incl = wave_incl_scan(s), excl = dpp_d<0x138>(incl);  // wave_shr:1, 0 into lane 0
+    const unsigned long long pos = __ballot(s > 0.0), over = __ballot(s > 0.0 && base + (excl + s) > x);
+    const bool last = over == 0ull;
+    if (pos == 0ull) {
+      if (t == 0) L.unit = -1;
+    } else if (t == (last ? 63 - __builtin_clzll(pos) : __builtin_ctzll(over))) {
+      double P = 0.0, pre = 0.0;
+      int unit = -1;
+#pragma unroll
+      for (int j = 0; j < UPL; ++j) {
+        const double Pn = P + us[j];
+        if ((last || unit < 0) && us[j] > 0.0 && (last || base + (excl + Pn) > x)) {
+          unit = t * UPL + j;
+          pre = P;
         }
-        Pacc = Pn;
-        return true;
-      });
-      s_sc[0] = sbase;
-      s_sc[2] = (double)sstar;
+        P = Pn;
+      }
+      L.unit = unit;
+      L.excl = excl;
+      L.pre = pre;
+      L.last = last;
+    }
+  }
+  __syncthreads();
+  const int unit = L.unit;
+  if (unit < 0) return false;
+  if (t == unit) {
+    const int64_t first = unit_first<T>(g, u0);
+    const double excl = L.excl, P = L.pre;
+    const bool last = L.last;
+    double Q = 0.0;
+    int y = -1;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      Q += q[e];
+      if ((last || y < 0) && q[e] > 0.0 && (last || base + (excl + (P + Q)) > x)) y = int(first + e);
+    }
+    *out = y;
+  }
+  return true;
+}
+
+template <typename T, int BD, typename PF>
+__device__ __forceinline__ void sample_from_parts(const T* trow, const T* drow, int64_t V, bool resid, float mst,
+                                                  float msd, float rho0, float u, int S, SampleLds& L, int32_t* out,
+                                                  PF&& part) {
+  constexpr int kRunRegs = 4;
+  const int t = threadIdx.x;
+  const Geom g = row_geom(trow, V);
+  const bool same_phase = ((reinterpret_cast<uintptr_t>(trow) ^ reinterpret_cast<uintptr_t>(drow)) & 15u) == 0;
+  const int slo = (int)((int64_t)t * S / 64), shi = (int)((int64_t)(t + 1) * S / 64);
+  for (int pass = 0; pass < 2; ++pass) {
+    if (t < 64) {
+      SlicePart run[kRunRegs];
+#pragma unroll
+      for (int j = 0; j < kRunRegs; ++j) run[j] = slo + j < shi ? part(slo + j) : SlicePart{0.0, 0.0, 0.0, 0.0};
+      // every partial of the run in slice order
+      auto each = [&](auto&& f) {
+#pragma unroll
+        for (int j = 0; j < kRunRegs; ++j)
+          if (slo + j < shi) f(slo + j, run[j]);
+        for (int s = slo + kRunRegs; s < shi; ++s) f(s, part(s));
+      };
+      // fresh normalisers and the exact ratio
+      double rho = 0.0;
+      if (resid) {
+        double te = 0.0, td = 0.0;
+        each([&](int, const SlicePart& p) {
+          te += p.et;
+          td += p.ed;
+        });
+        rho = wave_all_d(te, OpSumD()) / wave_all_d(td, OpSumD());
+      }
+      // slice masses: first-order correction of the rho0 sums, or the target row's own
+      auto mass = [&](const SlicePart& p, bool rs) -> double {
+        if (!rs) return p.et;
+        const double m = p.q - (rho - (double)rho0) * p.qd;
+        return m > 0.0 ? m : 0.0;
+      };
+      double sm = 0.0;
+      unsigned long long pos = 0;
+      bool rs = resid;
+      for (;;) {
+        sm = 0.0;
+        each([&](int, const SlicePart& p) { sm += mass(p, rs); });
+        pos = __ballot(sm > 0.0);
+        if (pos != 0ull || !rs) break;
+        rs = false;  // no residual mass: sample from the target row
+      }
+      const double excl = dpp_d<0x138>(wave_incl_scan(sm)), end = excl + sm;
+      const int tlast = pos ? 63 - __builtin_clzll(pos) : 0;
+      const double x = (double)u * rl_d(end, tlast);
+      const unsigned long long over = __ballot(sm > 0.0 && end > x);
+      if (t == (over ? __builtin_ctzll(over) : tlast)) {
+        // the slice inside this lane's run, repeating its sequential sums exactly
+        double Pacc = 0.0, sbase = 0.0;
+        int sstar = -1;
+        bool done = false;
+        each([&](int s, const SlicePart& p) {
+          const double m = mass(p, rs);
+          const double Pn = Pacc + m;
+          if (!done && m > 0.0) {
+            sstar = s;
+            sbase = excl + Pacc;
+            done = over != 0ull && excl + Pn > x;
+          }
+          Pacc = Pn;
+        });
+        L.base = sbase;
+        L.x = x;
+        L.rho = rho;
+        L.slice = sstar;
+        L.resid = rs;
+      }
     }
     __syncthreads();
-    const double sbase = s_sc[0];
-    const int64_t ulo = (int64_t)s_sc[2] * kSliceUnits;
-    const int64_t uhi = ulo + kSliceUnits < nu ? ulo + kSliceUnits : nu;
-    if (resid)
-      y = locate_units<T, true, BD>(trow, drow, g, same_phase, ulo, uhi, mst, msd, rho, sbase, x, sd, si, s_y);
-    else
-      y = locate_units<T, false, BD>(trow, trow, g, true, ulo, uhi, mst, mst, 0.0, sbase, x, sd, si, s_y);
-    if (y < 0 && resid) {
-      resid = false;
-      continue;
-    }
-    break;
+    if (L.slice < 0) break;
+    resid = L.resid != 0;
+    const bool found = resid ? sample_slice<T, true, BD>(trow, drow, g, same_phase, mst, msd, L, out)
+                             : sample_slice<T, false, BD>(trow, trow, g, true, mst, mst, L, out);
+    if (found) return;
+    if (!resid) break;
+    resid = false;
+    __syncthreads();  // the shared record is written again
   }
-  return y;
+  if (t == 0) *out = -1;
 }
 
 template <typename T, Src SRC>
 __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S, const SlicePart* __restrict__ ws) {
   constexpr int BD = kSampleBD;
-  __shared__ double sd[2 * (BD / 64)];
-  __shared__ int si[BD / 64];
-  __shared__ double s_sc[3];
-  __shared__ int s_y;
+  __shared__ SampleLds s_l;
   __shared__ SeqInfo s_q;
   const int t = threadIdx.x;
   const int b = blockIdx.x;
   if (b >= a.B) return;
-  // this thread's first slice partial, written by k_final_parts: its load does not wait
-  // for the decisions, so the two round trips overlap (unused for an invalid sequence
-  // and in GREEDY mode, where no partials were written; always inside the workspace)
-  const int slo = (int)((int64_t)t * S / BD), shi = (int)((int64_t)(t + 1) * S / BD);
+  // the first slice partial of each lane of wave 0, written by k_final_parts: its load does
+  // not wait for the decisions, so the two round trips overlap (unused for an invalid
+  // sequence and in GREEDY mode, where no partials were written; inside the workspace)
+  const int slo = (int)((int64_t)t * S / 64), shi = t < 64 ? (int)((int64_t)(t + 1) * S / 64) : 0;
   const SlicePart first = slo < shi ? ws[(int64_t)b * S + slo] : SlicePart{0.0, 0.0, 0.0, 0.0};
   const SeqInfo q = SRC == Src::Record ? *pass_info(a, b) : seq_info(a, b, &s_q);
   if (SRC == Src::Record && (q.nacc < 0 || a.mode == CMSD_MODE_GREEDY)) return;  // written by k_pass_decide
@@ -1801,12 +1788,9 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
   const T* trow = reinterpret_cast<const T*>(a.target) + q.tr * a.tstride;
   const T* drow = reinterpret_cast<const T*>(a.draft) + q.dr * a.dstride;
   const float u = a.unif[q.off + q.kb];
-  const int y = sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, sd, si, s_sc, &s_y,
-                                         [&](int s) { return s == slo ? first : ws[(int64_t)b * S + s]; });
-  if (t == 0) {
-    a.n_acc[b] = nacc;
-    a.next_tok[b] = y;
-  }
+  if (t == 0) a.n_acc[b] = nacc;
+  sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b,
+                           [&](int s) { return s == slo ? first : ws[(int64_t)b * S + s]; });
 }
 
 // Both in one launch, for small launches: SW workgroups of kFinalWaves waves per sequence.
@@ -1815,8 +1799,8 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
 // k_final_sample's order, so the outputs are the same bits).  The row pass before set the
 // count to zero.  Workgroup 0 of a sequence also writes what the decisions decide.  Bound
 // by its chain of memory round trips; us, MI355X, against the pair (V, sequences, bf16):
-// 32000 x 1 12.4 -> 10.0, 32000 x 8 13.5 -> 10.7, 50257 x 64 18.4 -> 16.0, 152064 x 64 (19
-// slice waves per compute unit) 23.4 -> 23.3; then the counting and the waits of resident
+// 32000 x 1 12.4 -> 10.0, 32000 x 8 13.5 -> 11.0, 50257 x 64 18.4 -> 16.0, 152064 x 64 (19
+// slice waves per compute unit) 24.3 -> 24.9 and a launch less; then the counting and the waits of resident
 // workgroups cost more than a launch: 32000 x 512 (32 per unit) 24.5 -> 31, 128256 x 256
 // (63 per unit) 37 -> 49.  Workgroups of 1, 2, 4 and 8 waves: 11.3, 10.6, 10.0 and 11.9 at
 // 32000 x 1, 18.3, 17.2, 16.0 and 15.9 at 50257 x 64.
@@ -1831,10 +1815,8 @@ __device__ __forceinline__ int* final_count(const VerifyArgs& a, int b) {
 template <typename T, Src SRC>
 __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW, SlicePart* __restrict__ ws) {
   constexpr int BD = kFinalBD;
-  __shared__ double sd[2 * kFinalWaves];
-  __shared__ int si[kFinalWaves];
-  __shared__ double s_sc[3];
-  __shared__ int s_y;
+  __shared__ SampleLds s_l;
+  __shared__ int s_done;
   __shared__ SeqInfo s_q;
   const int t = threadIdx.x;
   const int b = int(blockIdx.x / (unsigned)SW), part = int(blockIdx.x % (unsigned)SW);
@@ -1872,15 +1854,14 @@ __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW,
   }
   wait_stores();  // every wave's partials, before its workgroup is counted
   __syncthreads();
-  if (t == 0) si[0] = count_agent(final_count<SRC>(a, b));
+  if (t == 0) s_done = count_agent(final_count<SRC>(a, b));
   __syncthreads();
-  if (si[0] != SW - 1) return;
+  if (s_done != SW - 1) return;
   const float u = a.unif[q.off + q.kb];
-  const int y = sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, sd, si, s_sc, &s_y, [&](int s) {
+  sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b, [&](int s) {
     const double* p = reinterpret_cast<const double*>(P + s);
     return SlicePart{ld_agent(p), ld_agent(p + 1), ld_agent(p + 2), ld_agent(p + 3)};
   });
-  if (t == 0) a.next_tok[b] = y;
 }
 
 // ----------------------------------------------------------------------------- K5 draft sampling
@@ -1908,10 +1889,7 @@ template <typename T>
 __device__ __forceinline__ void fused_tail(const VerifyArgs& a, int b, int S, SlicePart* __restrict__ ws) {
   constexpr int BD = kFusedBD, NW = BD / 64;
   __shared__ SeqInfo s_q;
-  __shared__ double sd[2 * NW];
-  __shared__ int si[NW];
-  __shared__ double s_sc[3];
-  __shared__ int s_y;
+  __shared__ SampleLds s_l;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const SeqInfo q = seq_info_pass(a, b, true, &s_q);
   if (q.nacc < 0 || a.mode == CMSD_MODE_GREEDY) {
@@ -1948,12 +1926,9 @@ __device__ __forceinline__ void fused_tail(const VerifyArgs& a, int b, int S, Sl
   }
   __syncthreads();  // the partials of every slice, written by this workgroup
   const float u = a.unif[q.off + q.kb];
-  const int y = sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, sd, si, s_sc, &s_y,
-                                         [&](int s) { return P[s]; });
-  if (t == 0) {
-    a.n_acc[b] = q.nacc;
-    a.next_tok[b] = y;
-  }
+  if (t == 0) a.n_acc[b] = q.nacc;
+  sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b,
+                           [&](int s) { return P[s]; });
 }
 
 template <typename T>
@@ -2021,15 +1996,11 @@ __global__ __launch_bounds__(kSampleBD) void k_draft_pick(const T* __restrict__ 
                                                           const float* __restrict__ unif, int S,
                                                           const SlicePart* __restrict__ ws, int32_t* __restrict__ out) {
   constexpr int BD = kSampleBD;
-  __shared__ double sd[2 * (BD / 64)];
-  __shared__ int si[BD / 64];
-  __shared__ double s_sc[3];
-  __shared__ int s_y;
+  __shared__ SampleLds s_l;
   const int64_t r = blockIdx.x;
   const T* row = logits + r * stride;
-  const int y = sample_from_parts<T, kSampleBD>(row, row, V, false, stats[r].max_logit * kLog2e, 0.f, 0.f, unif[r], S, sd, si,
-                                                s_sc, &s_y, [&](int s) { return ws[r * S + s]; });
-  if (threadIdx.x == 0) out[r] = y;
+  sample_from_parts<T, BD>(row, row, V, false, stats[r].max_logit * kLog2e, 0.f, 0.f, unif[r], S, s_l, out + r,
+                           [&](int s) { return ws[r * S + s]; });
 }
 
 // ----------------------------------------------------------------------------- host helpers
