@@ -97,3 +97,29 @@ def test_draft_sample_random_rows(cm, seed):
         want, slack = O.draft_sample(Hn.decode(stored[r], dtype), float(u[r]))
         t.decision(f"y[{r}]", int(y[r]), want, slack)
     t.assert_ok()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("slices", [1, 4, 5, 32, 33])
+def test_draft_sample_slice_edges(cm, dtype, slices):
+    # vocabularies whose 16-byte vectors (and the head and tail units) end on either side
+    # of a slice of 256 units: one wave's slices, a second wave's first, the longest row of
+    # the one-launch path and the first past it
+    vec = 4 if dtype == "f32" else 8
+    dev = torch.device("cuda:0")
+    for units in (-1, 0, 1):
+        V = vec * (256 * slices - 2 + units) + 1
+        g = np.random.default_rng(V)
+        z = g.normal(0, 2.0, (6, V)).astype(np.float32)
+        z[4:] = -np.inf
+        z[4, V - 1], z[5, 0] = 1.0, 1.0                   # all mass on the last, the first token
+        stored = z if dtype == "f32" else W.bf16_bits_from_f32(z)
+        u = np.array([0.0, 1.0 - 2.0 ** -24, 0.5, 0.99999, 0.3, 0.7], dtype=np.float32)
+        x = Hn.to_device(stored, dtype, dev)
+        y = cm.cmsd_draft_sample(x, cm.cmsd_confidence(x), torch.from_numpy(u).to(dev))
+        torch.cuda.synchronize()
+        t = Hn.Tally()
+        for r in range(6):
+            want, slack = O.draft_sample(Hn.decode(stored[r], dtype), float(u[r]))
+            t.decision(f"V={V} y[{r}]", int(y[r]), want, slack)
+        t.assert_ok()

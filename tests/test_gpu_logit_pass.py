@@ -135,6 +135,45 @@ def test_decision_paths_bitwise_equal(cm, name, mode, adaptive):
         assert torch.equal(rec[k].view(torch.int32), auto[k].view(torch.int32)), k
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("slices", [1, 4, 5, 9])
+def test_final_launches_bitwise_equal(cm, dtype, slices):
+    # one final-token launch and the pair, at the edges of a slice (256 units of 16 bytes)
+    # and of a workgroup's four slices, k_max = 1 (the count beside the sequence record)
+    # and more: the same bits, and the oracle's decisions
+    vec = 4 if dtype == "f32" else 8
+    for units, K in ((-1, 1), (0, 3), (1, 2)):
+        V, B = vec * (256 * slices - 2 + units), 3
+        g = np.random.default_rng(V)
+        zd, zt, dr, u = _case(g, B, K, V, dtype)
+        dev = torch.device("cuda:0")
+        args = (Hn.to_device(zd, dtype, dev), Hn.to_device(zt, dtype, dev), torch.from_numpy(dr.reshape(-1)).to(dev),
+                torch.from_numpy(u.reshape(-1)).to(dev))
+        rec = _forced_decisions(cm, 1, lambda: _pass(cm, *args, B, K, O.MODE_CM)[0])
+        one = _forced_decisions(cm, 2, lambda: _pass(cm, *args, B, K, O.MODE_CM)[0])
+        for k in ("draft_stats", "draft_len", "target_stats", "n_accepted", "next_token"):
+            assert torch.equal(rec[k].view(torch.int32), one[k].view(torch.int32)), (V, K, k)
+        _run_case(cm, zd, zt, dr, u, B, K, V, dtype)
+
+
+def test_final_launch_rule_boundary(cm):
+    # batches of one-slice vocabularies on either side of 20 slice waves per compute unit,
+    # where the choice between one final-token launch and the pair falls: the same first
+    # sequences, the same outputs
+    n = 20 * torch.cuda.get_device_properties(0).multi_processor_count
+    V, K, B = 64, 1, n + 1
+    g = np.random.default_rng(3)
+    dev = torch.device("cuda:0")
+    dd = torch.from_numpy(g.normal(0, 2, (B * K, V)).astype(np.float32)).to(dev)
+    td = torch.from_numpy(g.normal(0, 2, (B * (K + 1), V)).astype(np.float32)).to(dev)
+    dr = torch.from_numpy(g.integers(0, V, B * K).astype(np.int32)).to(dev)
+    u = torch.from_numpy((g.integers(0, 1 << 24, B * (K + 1)) * 2.0 ** -24).astype(np.float32)).to(dev)
+    past = _pass(cm, dd, td, dr, u, B, K, O.MODE_CM)[0]
+    at = _pass(cm, dd[:n * K], td[:n * (K + 1)], dr[:n * K], u[:n * (K + 1)], n, K, O.MODE_CM)[0]
+    for k in ("n_accepted", "next_token", "draft_len"):
+        assert torch.equal(past[k][:n], at[k]), k
+
+
 @pytest.mark.parametrize("forced", [1, 2])
 def test_decision_paths_invalid_sequence(cm, forced):
     V, K, B = 500, 4, 3
