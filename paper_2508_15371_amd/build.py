@@ -67,9 +67,35 @@ def build_probe(verbose: bool = False) -> str:
     return PROBE_LIB
 
 
+BINDING_SRC = os.path.join(PKG, "csrc", "binding.cpp")
+BINDING_LIB = os.path.join(PKG, "_binding.so")
+
+
+def build_binding(verbose: bool = False) -> str:
+    """Compile the native argument marshalling of cmsd.py (host code, against this
+    interpreter and torch); returns its path."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    tmp = BINDING_LIB + ".tmp"
+    cmd = [os.environ.get("CXX") or shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INC,
+           "-I", os.path.join(tdir, "include"), "-I", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], "-o", tmp, BINDING_SRC, "-L", os.path.join(tdir, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed ({r.returncode}):\n{r.stderr}")
+    os.replace(tmp, BINDING_LIB)
+    return BINDING_LIB
+
+
 def build(verbose: bool = False) -> str:
-    """Compile libcmsd.so, then the native test consumer and the benchmark's read
-    probe; returns the library's path.  Always recompiles."""
+    """Compile libcmsd.so, then the native test consumer, the benchmark's read probe and
+    the native marshalling; returns the library's path.  Always recompiles."""
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", *FLAGS, "-I", INC, "-o", tmp, SRC]
     if verbose:
@@ -83,6 +109,7 @@ def build(verbose: bool = False) -> str:
     os.replace(tmp, LIB)
     build_native(verbose)
     build_probe(verbose)
+    build_binding(verbose)
     return LIB
 
 

@@ -69,3 +69,73 @@ def test_draft_sample_buffers():
     x = _f(5, 70)
     with pytest.raises(ValueError, match="device"):
         cm.cmsd_draft_sample(x, _f(5, 8), _f(5), drafted=_i(5), workspace=torch.zeros(100, dtype=torch.float64))
+
+
+def test_native_marshalling_leaves_the_rest_to_python():
+    # built with the library; host tensors, missing or misfitting arguments and numbers of
+    # another type are not its case: it answers None and the Python path checks and raises
+    n = cm._native
+    assert n is not None
+    x, lam = _f(4, 100), (0.2, 0.5, 0.3)
+    for args in ((x, _f(4, 8), lam, 1.0, 0), (x, None, lam, 1.0, 0), (x, _f(4, 8), list(lam), 1.0, 0),
+                 (x, _f(4, 8), lam, 1, 0), (x, _f(4, 8), lam), (), (x, _f(4, 8), lam, 1.0, 0, 0)):
+        assert n.confidence(*args) is None
+    assert n.draft_len(3, 1, 4, 1.0, _f(12, 8), _i(3), _i(4), 0) is None
+    assert n.draft_len(1 << 40, 1, 4, 1.0, _f(12, 8), _i(3), _i(4), 0) is None
+    with pytest.raises(TypeError):
+        n.bind(0)
+    with pytest.raises(ValueError):
+        n.bind(*[0] * 7)
+
+
+@pytest.mark.gpu
+def test_native_marshalling_same_calls():
+    # the same call through the native and the Python marshalling: equal outputs, and the
+    # same refusals (status and message) for misfitting device buffers
+    dev = torch.device("cuda:0")
+    B, K, V = 3, 4, 500
+    g = torch.Generator().manual_seed(0)
+    dd, td = torch.randn(B * K, V, generator=g).to(dev), torch.randn(B * (K + 1), V, generator=g).to(dev)
+    dr = torch.randint(0, V, (B * K,), generator=g, dtype=torch.int32).to(dev)
+    u = torch.rand(B * (K + 1), generator=g).to(dev)
+    ws, fws = cm.verify_workspace(B, K, V, dev), cm.fused_workspace(B, K, V, dev)
+
+    def outputs():
+        z = lambda t: t.to(dev)
+        st, k, off, ts = z(_f(B * K, 8)), z(_i(B)), z(_i(B + 1)), z(_f(B * (K + 1), 8))
+        na, nt, var, y = z(_i(B)), z(_i(B)), z(_f(B * K)), z(_i(B * K))
+        cm.cmsd_confidence(dd, st)
+        cm.cmsd_draft_len(st, B, k_min=K, k_max=K, alpha=1.0, draft_len=k, target_offsets=off)
+        cm.cmsd_verify(dd, st, td, off, k, dr, u, batch=B, k_max=K, target_stats=ts, n_accepted=na, next_token=nt,
+                       workspace=ws)
+        cm.cmsd_confidence_var(dd, st, var)
+        cm.cmsd_draft_sample(dd, st, u[:B * K].contiguous(), y,
+                             torch.empty(cm.cmsd_draft_sample_workspace_bytes(B * K, V) // 8, dtype=torch.float64,
+                                         device=dev))
+        got = [st, k, off, ts, na, nt, var, y]
+        for f, w in ((cm.cmsd_logit_pass, ws), (cm.cmsd_logit_pass_fused, fws)):
+            o = f(dd, td, dr, u, batch=B, k_max=K, draft_stats=z(_f(B * K, 8)), draft_len=z(_i(B)),
+                  target_stats=z(_f(B * (K + 1), 8)), n_accepted=z(_i(B)), next_token=z(_i(B)), workspace=w)
+            got += [o[n] for n in ("draft_stats", "draft_len", "target_stats", "n_accepted", "next_token")]
+            assert o["workspace"] is w
+        torch.cuda.synchronize()
+        errs = []
+        for call in (lambda: cm.cmsd_confidence(dd, z(_f(2, 8))), lambda: cm.cmsd_confidence(dd.t(), st),
+                     lambda: cm.cmsd_confidence(dd, st, beta_margin=-1.0),
+                     lambda: cm.cmsd_draft_len(st, B, k_min=5, k_max=K, alpha=1.0, draft_len=k, target_offsets=off),
+                     lambda: cm.cmsd_logit_pass(dd, td, dr, u, batch=B, k_max=K, draft_stats=st, draft_len=k,
+                                                target_stats=ts, n_accepted=na, next_token=nt, workspace=ws[:1])):
+            with pytest.raises(Exception) as e:
+                call()
+            errs.append((type(e.value), str(e.value)))
+        return got, errs
+
+    native, errs = outputs()
+    keep, cm._native = cm._native, None
+    try:
+        plain, plain_errs = outputs()
+    finally:
+        cm._native = keep
+    for a, b in zip(native, plain):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert errs == plain_errs
