@@ -215,6 +215,34 @@ __device__ __forceinline__ void st_agent(double* p, double v) {
 __device__ __forceinline__ double ld_agent(const double* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// A 32-byte record of 32-bit words, kept plainly or handed off.
+template <bool AGENT, typename R>
+__device__ __forceinline__ void put_record(R* p, const R& r) {
+  static_assert(sizeof(R) == 32 && alignof(R) % 4 == 0, "eight words");
+  if constexpr (AGENT) {
+    uint32_t w[8];
+    __builtin_memcpy(w, &r, 32);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      __hip_atomic_store(reinterpret_cast<uint32_t*>(p) + i, w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    *p = r;
+  }
+}
+template <bool AGENT, typename R>
+__device__ __forceinline__ R get_record(const R* p) {
+  if constexpr (AGENT) {
+    uint32_t w[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      w[i] = __hip_atomic_load(reinterpret_cast<const uint32_t*>(p) + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    R r;
+    __builtin_memcpy(&r, w, 32);
+    return r;
+  } else {
+    return *p;
+  }
+}
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ int count_agent(int* p) {
   return __hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -576,7 +604,7 @@ __device__ __forceinline__ cmsd_row_stats row_stats_record(float m, float z2, do
 #ifndef CMSD_KEEP_MAX_ROUND
 #define CMSD_KEEP_MAX_ROUND 1
 #endif
-template <typename T, int BD, bool VAR, int DEPTH = CMSD_STREAM_DEPTH>
+template <typename T, int BD, bool VAR, int DEPTH = CMSD_STREAM_DEPTH, bool AGENT = false>
 __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, const ConfArgs& a,
                                          cmsd_row_stats* __restrict__ out, float* __restrict__ var_out) {
   using E = Elem<T>;
@@ -769,7 +797,7 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
     if (t == 0) {
       // a second value at kMaskedLogit or below is a clamped -inf: the row has one finite logit
       const float z2 = nmax >= 2 ? m : fmaxf(cmx, s_oth);
-      *out = row_stats_record(m, z2 <= kMaskedLogit ? -INFINITY : z2, A, Tsum, flags, top1, a);
+      put_record<AGENT>(out, row_stats_record(m, z2 <= kMaskedLogit ? -INFINITY : z2, A, Tsum, flags, top1, a));
       if (VAR) {
         const double v = (vS2 - vS1 * (vS1 / vN)) / vN;
         *var_out = (float)(v > 0.0 ? v : 0.0);
@@ -1023,7 +1051,7 @@ __device__ __forceinline__ int accept_test(int mode, int beta, float tau_base, f
 // report) end there, else the row is packed row off[b] + i and its accept test is made
 // here.  PASS = true: dense row q = b*(k_max+1) + i of the single-call pass, whose
 // accept test waits for the drafter stats (PassSlot).
-template <typename T, int BD, bool PASS, int DEPTH = CMSD_STREAM_DEPTH>
+template <typename T, int BD, bool PASS, int DEPTH = CMSD_STREAM_DEPTH, bool AGENT = false>
 __device__ __forceinline__ void target_row(const VerifyArgs& a, int64_t q) {
   using E = Elem<T>;
   __shared__ double sd[BD / 64];
@@ -1126,7 +1154,8 @@ __device__ __forceinline__ void target_row(const VerifyArgs& a, int64_t q) {
   }
   if (t == 0 && PASS) {
     // the slot past the last draft has no drafted token: its zd starts the final-token count
-    a.pslots[r] = PassSlot{A, m, gz, in_k ? zd : 0.f, ngt, top1, !valid ? -2 : (has_draft ? 1 : -1)};
+    put_record<AGENT>(a.pslots + r,
+                      PassSlot{A, m, gz, in_k ? zd : 0.f, ngt, top1, !valid ? -2 : (has_draft ? 1 : -1)});
   } else if (t == 0) {
     cmsd_target_stats res{};
     res.max_logit = m;
@@ -1333,17 +1362,18 @@ __device__ __forceinline__ SeqInfo seq_info(const VerifyArgs& a, int b, SeqInfo*
 // length and every accept test (as the separate calls would); with `write` it also stores
 // the draft length and the target-row records.  The slots are only read, so every
 // workgroup of the final-token kernels forms the same decisions from them.
+template <bool AGENT = false>
 __device__ __forceinline__ SeqInfo seq_info_pass(const VerifyArgs& a, int b, bool write, SeqInfo* lds) {
   const int t = threadIdx.x, lane = t & 63;
   if (t < 64) {
     const int K = a.k_max;
     const bool greedy = a.mode == CMSD_MODE_GREEDY;
     const int64_t off = (int64_t)b * (K + 1);
-    const PassSlot sl = lane <= K ? a.pslots[off + lane] : PassSlot{1.0, 0.f, -INFINITY, -INFINITY, 0, -1, -1};
+    const PassSlot sl = lane <= K ? get_record<AGENT>(a.pslots + off + lane) : PassSlot{1.0, 0.f, -INFINITY, -INFINITY, 0, -1, -1};
     float dmx = 0.f, dA = 1.f, cf = 0.f, u = 0.f;
     int y = -1;
     if (lane < K) {
-      const cmsd_row_stats ds = a.dstats[(int64_t)b * K + lane];
+      const cmsd_row_stats ds = get_record<AGENT>(a.dstats + (int64_t)b * K + lane);
       dmx = ds.max_logit;
       dA = ds.sum_exp;
       cf = ds.conf;
@@ -1870,15 +1900,16 @@ __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW,
 // and exact in-slice locate as the final token, with u one uniform per row.
 // ----------------------------------------------------------------------------- fused pass (small batches)
 // The whole dense logit pass in one launch.  The grid is k_row_pass's (drafter rows,
-// then target rows, one 256-thread workgroup each).  Every row workgroup publishes its
-// record behind a device fence and counts itself into its sequence's counter; the
-// workgroup that completes the count (2 k_max + 1 rows) fences again, makes the
-// sequence's decisions (seq_info_pass, as k_pass_decide), computes the final row's
-// slice partials one wave per slice (parts_wave, as k_final_parts) and samples from
-// them (sample_from_parts, as k_final_sample), then sets the counter back to zero.
-// The arithmetic is the four-launch pass's, so the outputs are bit-identical to it.
-// The fences serialise chip-wide (about 35-50 ns per workgroup), which is why this
-// path is for launches of a few hundred rows, where it saves three dependent launches.
+// then target rows, one 256-thread workgroup each).  Every row workgroup hands its record
+// off and counts itself into its sequence's counter; the workgroup that completes the
+// count (2 k_max + 1 rows) makes the sequence's decisions (seq_info_pass, as
+// k_pass_decide), computes the final row's slice partials one wave per slice (parts_wave,
+// as k_final_parts) and samples from them (sample_from_parts, as k_final_sample), then
+// sets the counter back to zero.  The arithmetic is the four-launch pass's, so the outputs
+// are bit-identical to it.  For small batches: one compute unit does a sequence's final
+// token.  Device fences around the count, each a write-back of the L2, cost 30-50 ns of
+// the chip per workgroup; us with them and handed off, MI355X: 1 sequence of 4 drafts at
+// V = 1024 14.6 and 14.1, 8 of 8 drafts at V = 32000 23.8 and 22.3, 64 of them 148 and 39.
 constexpr int kFusedBD = 256;
 #ifndef CMSD_FUSED_SUB
 #define CMSD_FUSED_SUB 2
@@ -1891,7 +1922,7 @@ __device__ __forceinline__ void fused_tail(const VerifyArgs& a, int b, int S, Sl
   __shared__ SeqInfo s_q;
   __shared__ SampleLds s_l;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const SeqInfo q = seq_info_pass(a, b, true, &s_q);
+  const SeqInfo q = seq_info_pass<true>(a, b, true, &s_q);
   if (q.nacc < 0 || a.mode == CMSD_MODE_GREEDY) {
     if (t == 0) {
       a.n_acc[b] = q.nacc < 0 ? -1 : q.nacc;
@@ -1939,21 +1970,19 @@ __global__ __launch_bounds__(kFusedBD) void k_fused_pass(VerifyArgs a, int S, Sl
   const int64_t r = blockIdx.x;
   int b;
   if (r < nd) {
-    conf_row<T, kFusedBD, false>(
-        reinterpret_cast<const T*>(a.draft) + r * a.dstride, a.V, a.ca, a.dstats_out + r, nullptr);
+    conf_row<T, kFusedBD, false, CMSD_STREAM_DEPTH, true>(reinterpret_cast<const T*>(a.draft) + r * a.dstride, a.V,
+                                                          a.ca, a.dstats_out + r, nullptr);
     b = int(r / a.k_max);
   } else {
-    target_row<T, kFusedBD, true>(a, r - nd);
+    target_row<T, kFusedBD, true, CMSD_STREAM_DEPTH, true>(a, r - nd);
     b = int((r - nd) / (a.k_max + 1));
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();  // this row's record is visible before it is counted
-    s_last = atomicAdd(cnt + b, 1) == 2 * a.k_max;
+  if (threadIdx.x == 0) {  // the thread that stored the row's record
+    wait_stores();         // the record has arrived before the row is counted
+    s_last = count_agent(cnt + b) == 2 * a.k_max;
   }
   __syncthreads();
   if (!s_last) return;
-  __threadfence();  // every other row of the sequence was counted after its record
   if (threadIdx.x == 0) cnt[b] = 0;
   fused_tail<T>(a, b, S, ws);
 }
