@@ -13,7 +13,7 @@
  *                    accepted-prefix length, and the final token sampled from
  *                    the residual (or bonus) distribution     (Sec. III.A, III.B(c))
  *
- * cmsd_logit_pass does all three in one call (three or four launches, two in GREEDY
+ * cmsd_logit_pass does all three in one call (two or four launches, two in GREEDY
  * mode) for a dense target layout; cmsd_logit_pass_fused does it in one launch, for small
  * batches.
  *
@@ -249,12 +249,12 @@ cmsd_status cmsd_verify(const void* draft_logits, int64_t draft_stride, const cm
  * cmsd_logit_pass - the whole logit pass of one decoding iteration in one call, for
  * a dense target layout: cmsd_confidence on the drafter rows, cmsd_draft_len's draft
  * length and cmsd_verify on target rows stored k_max + 1 per sequence (Sec. III.B(1)
- * to (c), Sec. III.A), in three or four launches instead of five: one row pass over
+ * to (c), Sec. III.A), in two or four launches instead of five: one row pass over
  * the drafter and target rows together (they do not depend on each other), then the
- * two final-token kernels.  Each sequence's draft length and accept tests are formed
- * either by one wave per sequence between them (large launches) or by every
- * final-token workgroup from the row results (launches of at most 32 final-token
- * waves per compute unit, one launch fewer); cmsd_set_pass_decisions forces either.
+ * final token.  Each sequence's draft length and accept tests are formed either by
+ * every workgroup of one final-token launch from the row results (launches of at most
+ * 20 final-token waves per compute unit) or by one wave per sequence ahead of two
+ * final-token launches (larger ones); cmsd_set_pass_decisions forces either.
  * In GREEDY mode, whose final token is the row's top token, the decision wave ends
  * the call.
  *
@@ -322,13 +322,11 @@ cmsd_status cmsd_set_row_events(void* const* row_events);
  * (Sec. III.B(1) to (c), Sec. III.A, as cmsd_logit_pass; the paper's small-batch
  * latency, Fig. 2, is what it is for).  Every drafter and target row is one
  * 256-thread workgroup; the last row of a sequence to finish (an atomic count per
- * sequence, each row's results published behind a device fence) makes the draft
- * length and the accept tests and samples the final token in the same launch.  The
- * fences serialise across the chip (tens of ns per row), and one workgroup carries each
- * sequence's final token, so the single launch is the faster call only when that work
- * is tiny (one MI355X: 1024-logit rows); at V = 32000 cmsd_logit_pass (three launches
- * for small batches) was faster at every batch measured, 1 to 64.  It is for callers
- * that need exactly one launch.  Arguments, outputs and errors are cmsd_logit_pass's
+ * sequence, behind the row's stored and acknowledged results) makes the draft
+ * length and the accept tests and samples the final token in the same launch.  One
+ * workgroup carries each sequence's final token, so the single launch is for rows
+ * whose final-token work is tiny (1024 logits) and for callers that need exactly one
+ * launch.  Arguments, outputs and errors are cmsd_logit_pass's
  * (cmsd_set_row_events does not apply to it), except the workspace:
  *   workspace       device scratch of at least
  *                   cmsd_logit_pass_fused_workspace_bytes(batch, k_max, vocab) bytes,
@@ -413,8 +411,8 @@ cmsd_status cmsd_set_row_shape(int32_t threads, int32_t ring_depth);
  *   mode  0: chosen per call from the number of final-token workgroups (default);
  *         1: one decision wave per sequence writes a record the final-token kernels
  *            read (four launches);
- *         2: every final-token workgroup forms the decisions from the row results
- *            (three launches).
+ *         2: every workgroup of one final-token launch forms the decisions from the
+ *            row results (two launches).
  * Both run the same arithmetic: the outputs are bit-identical.
  * Errors: CMSD_ERR_ARG for any other mode.
  */

@@ -15,11 +15,13 @@
 //                   token's, the acceptance decision of that position, and the
 //                   row's slot in the workspace.
 //   k_final_parts   one wave per (sequence, vocabulary slice): first rejection from
-//                   the row slots (ballot; in cmsd_logit_pass the draft length and
-//                   accept tests too), then fp64 slice partials of the residual (or
-//                   bonus) row.
+//                   the row slots (ballot), then fp64 slice partials of the residual
+//                   (or bonus) row.
 //   k_final_sample  one workgroup per sequence: slice scan, then an exact in-slice
 //                   inverse-CDF locate that repeats the scan's sums bit for bit.
+//   k_final         both in one kernel for small launches (in cmsd_logit_pass the draft
+//                   length and accept tests too): the workgroup that finishes a
+//                   sequence's last slice samples.
 //   k_row_pass      cmsd_logit_pass's row pass: drafter rows (as k_confidence) and
 //                   dense target rows (as k_target_rows, decisions deferred) in one
 //                   grid.
@@ -27,10 +29,10 @@
 //                   per sequence: draft length, accept tests and first rejection,
 //                   written once for the final kernels (GREEDY: the final outputs).
 //   k_fused_pass    cmsd_logit_pass_fused, one launch for small batches: the row pass,
-//                   then the last row workgroup of each sequence (atomic count behind
-//                   a device fence) decides and samples with the same functions.
-//   k_draft_parts / k_draft_pick   the same slice machinery for one softmax sample
-//                   per drafter row.
+//                   then the last row workgroup of each sequence (an atomic count)
+//                   decides and samples with the same functions.
+//   k_draft_row     one softmax sample per drafter row of up to 128 KB, one workgroup
+//                   per row; k_draft_parts / k_draft_pick the same for longer rows.
 //
 // Compile-time tuning knobs (defaults are the measured best on gfx950): CMSD_STREAM_DEPTH
 // and CMSD_DEEP_DEPTH (row-pass rounds of loads in flight for short and long launches),
