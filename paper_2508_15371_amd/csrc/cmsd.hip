@@ -371,8 +371,12 @@ __device__ __forceinline__ void block_sum_n(double (&v)[N], double* lds) {
 // The loads go through a buffer descriptor of the round, whose range check ends at the
 // row: lanes past it read zeros and no memory, so the partial round is in flight with the
 // others (not a round trip of its own at the end), a refill past the last round is free,
-// and the addresses cost no vector instruction.  prep() runs once the first loads are
-// issued (work that must precede the first round overlaps their latency);
+// and the addresses cost no vector instruction.  The instruction's scalar offset counts in
+// that check on gfx950 (lane offset against records - scalar offset, none if that is
+// negative: seen word for word in records of 0 to 64 KB under offsets of 0 to 28 KB); a
+// descriptor per vector, which would not need it, costs 1 to 2 % (64 bf16 sequences of
+// 50257 36.0 -> 36.8 us, 512 packed masked ones of 32000 152.2 -> 154.3).  prep() runs once
+// the first loads are issued (work that must precede the first round overlaps their latency);
 // consume(raw[U], k, last) is called in round order, `last` (std::true_type) for the
 // rounds that may be partial.  Against pointer loads with a guarded partial round behind
 // the ring: 136 bf16 rows of 32000 8.9 -> 7.8 us, 128 fp32 ones 10.2 -> 8.5, 3334 packed
