@@ -51,7 +51,7 @@ PEAK_HBM_GBS = 8000.0   # MI355X HBM3E
 # HBM bytes per launch of each workload's roofline kernel, from two rocprofv3 --pmc
 # runs (FETCH_SIZE, WRITE_SIZE) scaled by what the same counters read for a 1 GiB
 # device copy (x2.0 and x1.0).  Valid only for the kernel code they were taken on
-# (kernel_code_hash(): sha256 prefix of the .hip file's code without comments);
+# (kernel_code_hash(): sha256 prefix of the kernel sources' code without comments);
 # otherwise "traffic" is reported null.
 TRAFFIC = {"kernel_code_sha256_16": "9caa4009932a4e5a",
            "k_row_pass_c4": 2170.51e6 + 0.270e6, "k_confidence_c4": 1052.88e6 + 0.131e6,
@@ -132,11 +132,12 @@ def _cpu_model() -> str:
 
 
 def kernel_code_hash() -> str:
-    """sha256 prefix of the kernel source's code: comments and blank space are
+    """sha256 prefix of the kernel sources' code: comments and blank space are
     dropped first, so an edit to comments alone keeps the measured traffic valid."""
     import hashlib
     import re
-    src = open(os.path.join(ROOT, "paper_2508_15371_amd", "csrc", "cmsd.hip")).read()
+    csrc = os.path.join(ROOT, "paper_2508_15371_amd", "csrc")
+    src = "".join(open(os.path.join(csrc, f)).read() for f in ("cmsd.hip", "row_buffer.h"))
     src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
     src = re.sub(r"//[^\n]*", " ", src)
     code = " ".join(src.split())

@@ -54,6 +54,7 @@
 #include <type_traits>
 
 #include "cmsd.h"
+#include "row_buffer.h"
 
 namespace {
 
@@ -190,15 +191,10 @@ __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(
 
 // Streaming 16-byte load with the nontemporal hint: logit rows are read once per
 // pass, and the hint keeps them from displacing reused lines in the caches.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 ld_stream(const uint4* p) {
   const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-
-// A raw buffer of 32-bit words (data format 4 in bits 18:15), and the nontemporal hint.
-constexpr int kBufferFlags = 0x00020000;
-constexpr int kBufferNt = 2;
 
 __device__ __forceinline__ uint4 select4(bool c, const uint4& a, const uint4& b) {
   return make_uint4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
@@ -369,13 +365,9 @@ __device__ __forceinline__ void block_sum_n(double (&v)[N], double* lds) {
 // sits behind a branch, so the number of loads in flight is the same on every path and
 // the wait before a round covers that round only while the later ones stay in flight.
 // The loads go through a buffer descriptor of the round, whose range check ends at the
-// row: lanes past it read zeros and no memory, so the partial round is in flight with the
-// others (not a round trip of its own at the end), a refill past the last round is free,
-// and the addresses cost no vector instruction.  The instruction's scalar offset counts in
-// that check on gfx950 (lane offset against records - scalar offset, none if that is
-// negative: seen word for word in records of 0 to 64 KB under offsets of 0 to 28 KB); a
-// descriptor per vector, which would not need it, costs 1 to 2 % (64 bf16 sequences of
-// 50257 36.0 -> 36.8 us, 512 packed masked ones of 32000 152.2 -> 154.3).  prep() runs once
+// row (load_round): lanes past it read zeros and no memory, so the partial round is in
+// flight with the others (not a round trip of its own at the end), a refill past the last
+// round is free, and the addresses cost no vector instruction.  prep() runs once
 // the first loads are issued (work that must precede the first round overlaps their latency);
 // consume(raw[U], k, last) is called in round order, `last` (std::true_type) for the
 // rounds that may be partial.  Against pointer loads with a guarded partial round behind
@@ -386,29 +378,20 @@ __device__ __forceinline__ void block_sum_n(double (&v)[N], double* lds) {
 #endif
 template <int U, int BD, int DEPTH, typename P, typename F>
 __device__ __forceinline__ void stream_rounds(const uint4* vp, int64_t nvec, int t, P&& prep, F&& consume) {
-  constexpr int64_t kRound = (int64_t)U * BD;
-  const int64_t nt = (nvec + kRound - 1) / kRound;
+  const int n = int(nvec), nt = (n + U * BD - 1) / (U * BD);  // a row: under 2^29 vectors
   if (nt <= 0) {
     prep();
     return;
   }
   uint4 buf[DEPTH][U];
-  auto refill = [&](int d, int64_t k) {
-    const int64_t left = nvec - k * kRound;  // vectors of the row from this round on
-    const int bytes = 16 * int(left < 0 ? 0 : (left < kRound ? left : kRound));
-    const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(vp) + k * kRound, 0, bytes, kBufferFlags);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, t * 16, u * BD * 16, kBufferNt);
-      buf[d][u] = make_uint4(v.x, v.y, v.z, v.w);
-    }
+  auto refill = [&](int d, int k) {
+    load_round<U, BD>(vp, n, k, t, buf[d]);
     __builtin_amdgcn_sched_barrier(0);  // rounds leave in order, before the next one is consumed
   };
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) refill(d, d);
   prep();
-  int64_t k0 = 0;
+  int k0 = 0;
   for (; k0 + DEPTH < nt; k0 += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
@@ -654,7 +637,7 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
     stream_rounds<U, BD, DEPTH>(vp, g.nvec, t, [&] {
       hv = E::load(row + (t < g.head ? t : 0));
       tv = E::load(row + (t < g.tail ? tail0 + t : 0));
-    }, [&](uint4 (&raw)[U], int64_t k, auto last) {
+    }, [&](uint4 (&raw)[U], int k, auto last) {
       // lanes of the partial round past the row: the probe sees zeros there, and the sums
       // the clamp value, which adds exactly 0 to A and T as a masked logit does (the
       // variance moments skip them)
@@ -824,7 +807,7 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
 #define CMSD_WAVES(W) __attribute__((amdgpu_waves_per_eu((W) ? (W) : 1, (W) ? (W) : 8)))
 template <typename T, int BD, bool VAR, int DEPTH>
 constexpr int kConfWaves = !std::is_same<T, Bf16>::value || VAR ? 0
-                           : DEPTH == 2 ? (BD == 256 ? 6 : 0) : (BD == 64 ? 3 : 0);
+                           : DEPTH == 2 ? (BD > 64 ? 6 : 0) : (BD == 64 ? 3 : 0);
 template <typename T, int BD, int DEPTH>
 constexpr int kRowWaves = BD == 64 ? 0 : std::is_same<T, Bf16>::value ? (DEPTH == 2 ? 6 : 3) : (DEPTH == 2 ? 5 : 2);
 
@@ -1012,7 +995,7 @@ __device__ __forceinline__ void target_stream(const T* row, const Geom& g, const
         float f[1] = {t < g.head ? hv : -INFINITY};
         target_chunk<1>(s, f, 0, count, gz, beta, wcnt);
       },
-      [&](uint4 (&raw)[U], int64_t k, auto last) {
+      [&](uint4 (&raw)[U], int k, auto last) {
         if (last && k == nr) {  // the partial round: -inf past the row
 #pragma unroll
           for (int u = 0; u < U; ++u)

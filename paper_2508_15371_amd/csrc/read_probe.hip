@@ -1,4 +1,5 @@
-// Read-ceiling probe for the benchmark (measurement only; not part of the cmsd C ABI).
+// Probes for the benchmark and the tests (not part of the cmsd C ABI): the read ceiling, and
+// the range check that the row kernels' loads rest on.
 //
 // A launch of `cmsd_probe_read_rows` reads every logit row the joint row pass reads,
 // in the same grid shape (one workgroup per row, drafter rows first, then target
@@ -11,9 +12,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-namespace {
+#include "row_buffer.h"
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+namespace {
 
 template <int BD, int UNROLL>
 __global__ __launch_bounds__(BD) void k_read_rows(const char* __restrict__ a, int64_t a_rows, int64_t a_stride,
@@ -40,6 +41,24 @@ __global__ __launch_bounds__(BD) void k_read_rows(const char* __restrict__ a, in
     acc ^= v.x ^ v.y ^ v.z ^ v.w;
   }
   if (acc == 0x9e3779b9u) sink[0] = acc;
+}
+
+// Rounds 0 .. rounds-1 of a row of nvec vectors at vp, loaded as the row kernels load
+// them and written out in order.
+template <int U, int BD>
+__global__ __launch_bounds__(BD) void k_row_rounds(const uint4* __restrict__ vp, int nvec, int rounds,
+                                                   uint4* __restrict__ out) {
+  for (int k = 0; k < rounds; ++k) {
+    uint4 v[U];
+    load_round<U, BD>(vp, nvec, k, threadIdx.x, v);
+#pragma unroll
+    for (int u = 0; u < U; ++u) out[(k * U + u) * BD + threadIdx.x] = v[u];
+  }
+}
+template <int U>
+void launch_rounds(int bd, hipStream_t st, const uint4* vp, int nvec, int rounds, uint4* out) {
+  const auto kernel = bd == 64 ? k_row_rounds<U, 64> : bd == 128 ? k_row_rounds<U, 128> : k_row_rounds<U, 256>;
+  hipLaunchKernelGGL(kernel, dim3(1), dim3((unsigned)bd), 0, st, vp, nvec, rounds, out);
 }
 
 template <int BD>
@@ -74,6 +93,24 @@ int cmsd_probe_read_rows(const void* a, int64_t a_rows, int64_t a_stride, const 
   if (bd == 64) launch<64>(unroll, grid, st, pa, a_rows, a_stride, pb, b_stride, row_bytes, s);
   else if (bd == 128) launch<128>(unroll, grid, st, pa, a_rows, a_stride, pb, b_stride, row_bytes, s);
   else launch<256>(unroll, grid, st, pa, a_rows, a_stride, pb, b_stride, row_bytes, s);
+  return hipGetLastError() == hipSuccess ? 0 : 3;
+}
+
+// Loads rounds 0 .. rounds-1 of a row of nvec 16-byte vectors at vp as a row kernel of bd
+// threads (64, 128 or 256) and u (4 or 8) vectors per thread does, into out[rounds*u*bd]:
+// the row's vectors, then zeros.  The caller's buffer at vp holds all rounds*u*bd vectors,
+// so that the loads stay inside it whatever the range check does.  Device pointers, 16-byte
+// aligned.  Returns 0 on launch, 1 on a bad argument, 3 on a launch error.
+int cmsd_probe_row_rounds(const void* vp, int64_t vp_vectors, int64_t nvec, int rounds, int bd, int u, void* out,
+                          int64_t out_vectors, void* stream) {
+  if ((bd != 64 && bd != 128 && bd != 256) || (u != 4 && u != 8) || rounds < 1 || rounds > 1024) return 1;
+  const int64_t all = (int64_t)rounds * u * bd;
+  if (!vp || !out || ((uintptr_t)vp | (uintptr_t)out) % 16 || nvec < 0 || nvec > all || vp_vectors < all ||
+      out_vectors < all)
+    return 1;
+  const hipStream_t st = static_cast<hipStream_t>(stream);
+  if (u == 8) launch_rounds<8>(bd, st, static_cast<const uint4*>(vp), (int)nvec, rounds, static_cast<uint4*>(out));
+  else launch_rounds<4>(bd, st, static_cast<const uint4*>(vp), (int)nvec, rounds, static_cast<uint4*>(out));
   return hipGetLastError() == hipSuccess ? 0 : 3;
 }
 

@@ -115,8 +115,10 @@ def test_rounds_across_the_ring(cm, row_shape, block, dtype, depth):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_round_edges_between_nans(cm, row_shape, block, dtype, depth):
     # rows whose vectors end on, one before and one after the edge of a round, for every
-    # count of rounds the ring can be left with, between NaNs: nothing past a row's ends
-    # may reach its record (one NaN would make its sums NaN)
+    # count of rounds the ring can be left with, between NaNs: a head, a tail or a vector
+    # taken one element past a row's ends would make its sums NaN.  (That the loads
+    # themselves stop at the row is test_gpu_row_rounds.py's: their lanes past it are
+    # replaced before the sums, whatever they loaded.)
     row_shape(block, depth)
     lam = (0.2, 0.5, 0.3)
     lam32 = tuple(Hn.f32(x) for x in lam)
