@@ -803,11 +803,17 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
 // 128256 26.0 at 6 against 27.3 at 4.  A long launch streams best with few (more rows at a
 // time spread the reads over more of the memory): 8448 rows of 128256 in us, bf16 316.4 at
 // 2, 313.0 at 3, 314.7 at 4, 327 at 5; fp32 635 at 1, 617 at 2, 622.7 at 3, 627 at 4; 8192
-// bf16 drafter rows of 32000 88.0 at 2, 86.1 at 3, 86.7 at 4.
+// bf16 drafter rows of 32000 88.0 at 2, 86.1 at 3, 86.7 at 4; 4096 fp32 drafter rows of
+// 128256 315.1 at 2, 317.3 at 3, 318.9 at 4; the 4352 target rows of cmsd_verify beside
+// them 338.4 at 2, 342.2 at 3, 344.7 at 4.
 #define CMSD_WAVES(W) __attribute__((amdgpu_waves_per_eu((W) ? (W) : 1, (W) ? (W) : 8)))
 template <typename T, int BD, bool VAR, int DEPTH>
-constexpr int kConfWaves = !std::is_same<T, Bf16>::value || VAR ? 0
-                           : DEPTH == 2 ? (BD > 64 ? 6 : 0) : (BD == 64 ? 3 : 0);
+constexpr int kConfWaves = !std::is_same<T, Bf16>::value ? (DEPTH == 3 && BD == 256 ? 2 : 0)
+                           : VAR                         ? 0
+                           : DEPTH == 2                  ? (BD > 64 ? 6 : 0)
+                                                         : (BD == 128 ? 0 : 3);
+template <typename T, int BD, int DEPTH>
+constexpr int kTargetWaves = !std::is_same<T, Bf16>::value && DEPTH == 3 && BD == 256 ? 2 : 0;
 template <typename T, int BD, int DEPTH>
 constexpr int kRowWaves = BD == 64 ? 0 : std::is_same<T, Bf16>::value ? (DEPTH == 2 ? 6 : 3) : (DEPTH == 2 ? 5 : 2);
 
@@ -1166,7 +1172,7 @@ __device__ __forceinline__ void target_row(const VerifyArgs& a, int64_t q) {
 }
 
 template <typename T, int BD, int DEPTH>
-__global__ __launch_bounds__(BD) void k_target_rows(VerifyArgs a) {
+__global__ __launch_bounds__(BD) CMSD_WAVES((kTargetWaves<T, BD, DEPTH>)) void k_target_rows(VerifyArgs a) {
   target_row<T, BD, false, DEPTH>(a, blockIdx.x);
 }
 
@@ -2092,10 +2098,11 @@ int fit_block(int bd, int64_t groups) {
   while (bd > 64 && !launch_fits(groups, bd)) bd >>= 1;
   return bd;
 }
+constexpr int64_t kLongRow = (int64_t)128 << 10;  // bytes
 int row_block(int64_t n_rows, int64_t row_bytes) {
   if (const int v = g_row_block.load(std::memory_order_relaxed)) return fit_block(v, n_rows);
   const int64_t waves = 16 * (int64_t)device_cus();  // 4 waves on each of 4 SIMDs per CU
-  if (row_bytes <= (int64_t)128 << 10) {
+  if (row_bytes <= kLongRow) {
     if (n_rows >= waves) return 64;
     if (n_rows >= waves / 2) return 128;
   }
@@ -2103,10 +2110,17 @@ int row_block(int64_t n_rows, int64_t row_bytes) {
 }
 
 // Rounds in flight per thread for a streaming-row launch.  Long launches (several
-// generations of workgroups: at least 16 rows per compute unit for the joint row pass,
-// 32 for the confidence pass alone, as 8448 rows of 128256 logits in one pass or 8192
-// drafter rows of 32000) stream better with three rounds in flight; shorter ones keep
-// two, whose smaller register count lets more of their rows run at once.  The depth only schedules loads: the
+// generations of workgroups) stream better with three rounds in flight and few waves (the
+// waves at CMSD_WAVES); shorter ones keep two, whose smaller register count lets more of
+// their rows run at once.  The line, in rows per compute unit: 16 for the joint row pass
+// and 32 for the confidence pass alone, as 8448 rows of 128256 logits in one pass or 8192
+// drafter rows of 32000; 8 where a row is over 128 KB, for the confidence pass and the
+// joint pass of fp32 (two rounds -> three, us: 2048 fp32 drafter rows of 128256
+// 155.0 -> 153.5, 4096 of them 320.3 -> 315.1, 8192 bf16 ones 326.7 -> 318.5, 2040 fp32
+// rows of the joint pass 163.7 -> 161.9, 3400 of 50257 114.4 -> 109.7).  cmsd_verify's packed
+// target rows take three from 8 per unit on where a row is over 256 KB of fp32 (1700 of
+// 128256 134.7 -> 133.0, 4352 of them 344.4 -> 338.4; of 40000 logits, 160 KB,
+// 110.9 -> 113.7; 3097 bf16 rows of 32000 slower too).  The depth only schedules loads: the
 // arithmetic, and so every result, is the same.  cmsd_set_row_shape forces it.
 #ifndef CMSD_DEEP_DEPTH
 #define CMSD_DEEP_DEPTH 3
@@ -2139,7 +2153,7 @@ void launch_confidence_d(int bd, const T* logits, int64_t n_rows, int64_t V, int
 template <typename T, bool VAR>
 void launch_confidence(int bd, const T* logits, int64_t n_rows, int64_t V, int64_t stride, const ConfArgs& a,
                        cmsd_row_stats* out, float* var, hipStream_t st) {
-  if (deep_ring(n_rows, 32))
+  if (deep_ring(n_rows, V * (int64_t)sizeof(T) > kLongRow ? 8 : 32))
     launch_confidence_d<T, VAR, CMSD_DEEP_DEPTH>(bd, logits, n_rows, V, stride, a, out, var, st);
   else
     launch_confidence_d<T, VAR, CMSD_STREAM_DEPTH>(bd, logits, n_rows, V, stride, a, out, var, st);
@@ -2155,11 +2169,11 @@ void launch_target_rows_d(int bd, const VerifyArgs& a, hipStream_t st) {
   else
     hipLaunchKernelGGL((k_target_rows<T, 256, DEPTH>), grid, dim3(256), 0, st, a);
 }
-// The packed target rows of cmsd_verify: two rounds in flight (three measured slower
-// on 3097 rows of 32000 bf16 logits), three only when forced.
+// The packed target rows of cmsd_verify.
 template <typename T>
 void launch_target_rows(int bd, const VerifyArgs& a, hipStream_t st) {
-  if (g_ring_depth.load(std::memory_order_relaxed) == 3)
+  const bool longest = std::is_same<T, float>::value && a.V * (int64_t)sizeof(T) > 2 * kLongRow;
+  if (deep_ring(longest ? a.target_rows : 0, 8))
     launch_target_rows_d<T, CMSD_DEEP_DEPTH>(bd, a, st);
   else
     launch_target_rows_d<T, CMSD_STREAM_DEPTH>(bd, a, st);
@@ -2186,7 +2200,7 @@ void launch_row_pass_d(int bd, const VerifyArgs& a, int64_t rows, hipStream_t st
 }
 template <typename T>
 void launch_row_pass(int bd, const VerifyArgs& a, int64_t rows, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  if (deep_ring(rows, 16))
+  if (deep_ring(rows, std::is_same<T, float>::value && a.V * (int64_t)sizeof(T) > kLongRow ? 8 : 16))
     launch_row_pass_d<T, CMSD_DEEP_DEPTH>(bd, a, rows, st, e0, e1);
   else
     launch_row_pass_d<T, CMSD_STREAM_DEPTH>(bd, a, rows, st, e0, e1);
