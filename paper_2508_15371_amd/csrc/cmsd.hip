@@ -2031,8 +2031,7 @@ __global__ __launch_bounds__(kSampleBD) void k_draft_pick(const T* __restrict__ 
 // per row: each wave requests its kDraftRowSub slices at once and leaves their sums in LDS,
 // and the workgroup samples from there.  Longer rows take more than one such step, which a
 // single compute unit streams more slowly than the slices' own workgroups do (64 fp32 rows
-// of 128256: 18.5 us against 11.8).  16 fp32 rows of 32000 6.6 us against the pair's 7.8
-// and a launch, 512 bf16 rows of 50257 14.6 against 17.1, of 16000 8.8 against 11.1.
+// of 128256: 18.5 us against 11.8).
 constexpr int kDraftRowBD = 512;
 constexpr int kDraftRowSub = 4;
 constexpr int kDraftRowSlices = kDraftRowBD / 64 * kDraftRowSub;
@@ -2385,6 +2384,18 @@ cmsd_status enqueue_logit_pass(const VerifyArgs& a, int32_t dtype, void* workspa
   return launched();
 }
 
+// Whether a draft sample of n_rows rows of S slices takes one launch (k_draft_row) or two.
+// A row's workgroup holds eight waves, and those past its slices do nothing: while every
+// row is in flight at once (two workgroups per compute unit; three fit) that is free, but
+// launches of more rows want 12 slices or more.  fp32 rows, us, one launch against two:
+// 512 of 1 slice 6.0 and 6.3, of 8 6.6 and 8.0, of 32 13.0 and 14.6; 1024 of 1 9.9 and
+// 6.9, of 8 11.7 and 10.7, of 12 13.3 and 12.5, of 16 15.6 and 16.5; 8192 of 1 59 and 21,
+// of 8 66 and 61, of 12 76 and 81, of 16 92 and 109.
+bool one_draft_launch(int64_t n_rows, int S) {
+  if (S > kDraftRowSlices || !launch_fits(n_rows, kDraftRowBD)) return false;
+  return n_rows <= 2 * (int64_t)device_cus() || S >= 12;
+}
+
 // The launches of cmsd_verify after its target rows (GREEDY: the outputs only).
 template <typename T>
 void launch_verify_final(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
@@ -2470,7 +2481,7 @@ cmsd_status cmsd_draft_sample(const void* logits, int32_t dtype, int64_t n_rows,
   SlicePart* ws = static_cast<SlicePart*>(workspace);
   const hipStream_t st = as_stream(stream);
   const dim3 gp((unsigned)(n_rows * SW)), gr((unsigned)n_rows);
-  if (S <= kDraftRowSlices && launch_fits(n_rows, kDraftRowBD)) {
+  if (one_draft_launch(n_rows, S)) {
     if (dtype == CMSD_F32)
       hipLaunchKernelGGL((k_draft_row<float>), gr, dim3(kDraftRowBD), 0, st, static_cast<const float*>(logits),
                          row_stride, vocab, stats, uniforms, S, drafted);

@@ -123,3 +123,29 @@ def test_draft_sample_slice_edges(cm, dtype, slices):
             want, slack = O.draft_sample(Hn.decode(stored[r], dtype), float(u[r]))
             t.decision(f"V={V} y[{r}]", int(y[r]), want, slack)
         t.assert_ok()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("slices", [1, 4, 11])
+def test_draft_sample_launch_rule(cm, dtype, slices):
+    # short rows take one launch up to two rows per compute unit and two launches beyond:
+    # the same rows give the same samples in either, and in launches of a few rows
+    vec = 4 if dtype == "f32" else 8
+    dev = torch.device("cuda:0")
+    n = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    V = vec * 256 * slices - vec * 2 - 1
+    g = torch.Generator(device=dev).manual_seed(slices)
+    x = (3.0 * torch.randn(n + 1, V, generator=g, device=dev)).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    u = torch.rand(n + 1, generator=g, device=dev)
+    st = cm.cmsd_confidence(x)
+    two = cm.cmsd_draft_sample(x, st, u)
+    one = cm.cmsd_draft_sample(x[:n], st[:n], u[:n])
+    few = cm.cmsd_draft_sample(x[n - 3:], st[n - 3:], u[n - 3:])
+    torch.cuda.synchronize()
+    assert torch.equal(two[:n], one) and torch.equal(two[n - 3:], few)
+    t = Hn.Tally()
+    for r in (0, 1, n - 1, n):
+        row = x[r].float().cpu().numpy()
+        want, slack = O.draft_sample(row.astype(np.float64), float(u[r]))
+        t.decision(f"y[{r}]", int(two[r]), want, slack)
+    t.assert_ok()
