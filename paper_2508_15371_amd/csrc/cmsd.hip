@@ -1218,6 +1218,18 @@ constexpr int kSampleBD = 256;
 struct SlicePart {
   double et, ed, q, qd;
 };
+// A field of a slice's partials, by its place, and none of them.
+template <int I>
+using PartField = std::integral_constant<int, I>;
+using PartEt = PartField<0>;
+using PartEd = PartField<1>;
+using PartQ = PartField<2>;
+using PartQd = PartField<3>;
+using PartNone = PartField<-1>;
+template <int I>
+__device__ __forceinline__ double field(const SlicePart& p, PartField<I>) {
+  return I == 0 ? p.et : I == 1 ? p.ed : I == 2 ? p.q : I == 3 ? p.qd : 0.0;
+}
 
 template <typename T>
 __device__ __forceinline__ int64_t unit_first(const Geom& g, int64_t u) {
@@ -1618,11 +1630,18 @@ struct SampleLds {
 // and base + C(y) > x, C the slice's cumulative weight in a fixed order (if none
 // qualifies, the last element with q_y > 0).  A zero residual falls back to the target
 // row.  Writes *out, -1 if every weight is 0.  Run by one workgroup of BD threads: one wave
-// searches the slices (each lane a contiguous run, its first kRunRegs partials in
-// registers) and the unit sums, thread i weighs unit i of the slice, and the thread of the
-// chosen unit repeats its own sums exactly: three barriers, where searches by the whole
-// workgroup took a dozen (MI355X: k_final, 1 sequence of 32000 9.9 -> 8.9 us, 64 of 152064
-// 24.9 -> 21.1; k_final_sample, 256 of 128256 7.0 -> 5.4).
+// searches the slices (each lane a contiguous run, in registers) and the unit sums, thread
+// i weighs unit i of the slice, and the thread of the chosen unit repeats its own sums
+// exactly: three barriers, where searches by the whole workgroup took a dozen (MI355X:
+// k_final, 1 sequence of 32000 9.9 -> 8.9 us, 64 of 152064 24.9 -> 21.1; k_final_sample, 256
+// of 128256 7.0 -> 5.4).  LONG: rows of more than kShortSlices slices (a vocabulary over
+// 262000 in fp32, over 524000 in bf16), which every wave searches, the runs past the
+// registers kRunStep partials at a time: by one wave, a partial at a time, their loads were
+// round trips in a row (one row of 4 million fp32
+// logits, draft sample 30.8 -> 11.2 us; of a million 10.1 -> 6.9).
+constexpr int kRunRegs = 4;
+constexpr int kShortSlices = 64 * kRunRegs;
+constexpr int kRunStep = 4;
 template <typename T, bool RESID, int BD>
 __device__ __forceinline__ bool sample_slice(const T* trow, const T* drow, const Geom& g, bool same_phase, float mst,
                                              float msd, SampleLds& L, int32_t* out) {
@@ -1693,69 +1712,146 @@ __device__ __forceinline__ bool sample_slice(const T* trow, const T* drow, const
   return true;
 }
 
-template <typename T, int BD, typename PF>
+// One value of every searching wave, known to all of them, in wave order (NW = 1: the
+// wave's own).  The leading barrier protects the slots from a previous use.
+template <int NW, typename V>
+__device__ __forceinline__ void share_waves(V v, V* lds) {
+  if constexpr (NW > 1) {
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+  }
+}
+template <int NW>
+__device__ __forceinline__ double search_sum(double v, double* lds) {
+  double r = wave_all_d(v, OpSumD());
+  if constexpr (NW > 1) {
+    share_waves<NW>(r, lds);
+    r = lds[0];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) r += lds[i];
+  }
+  return r;
+}
+// The lowest (HIGH off) or highest thread whose bit is set in the waves' ballots, or -1.
+template <int NW, bool HIGH>
+__device__ __forceinline__ int search_thread(unsigned long long mask, unsigned long long* lds) {
+  if constexpr (NW == 1) {
+    return mask == 0ull ? -1 : (HIGH ? 63 - __builtin_clzll(mask) : __builtin_ctzll(mask));
+  } else {
+    share_waves<NW>(mask, lds);
+    int r = -1;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int w = HIGH ? i : NW - 1 - i;
+      const unsigned long long b = lds[w];
+      r = b == 0ull ? r : 64 * w + (HIGH ? 63 - __builtin_clzll(b) : __builtin_ctzll(b));
+    }
+    return r;
+  }
+}
+
+template <typename T, int BD, bool LONG, typename PF>
 __device__ __forceinline__ void sample_from_parts(const T* trow, const T* drow, int64_t V, bool resid, float mst,
                                                   float msd, float rho0, float u, int S, SampleLds& L, int32_t* out,
                                                   PF&& part) {
-  constexpr int kRunRegs = 4;
+  constexpr int NW = LONG ? BD / 64 : 1;  // searching waves
+  __shared__ double s_v[NW];
+  __shared__ unsigned long long s_b[NW];
+  __shared__ double s_end;
   const int t = threadIdx.x;
   const Geom g = row_geom(trow, V);
   const bool same_phase = ((reinterpret_cast<uintptr_t>(trow) ^ reinterpret_cast<uintptr_t>(drow)) & 15u) == 0;
-  const int slo = (int)((int64_t)t * S / 64), shi = (int)((int64_t)(t + 1) * S / 64);
+  const int slo = (int)((int64_t)t * S / (64 * NW)), shi = (int)((int64_t)(t + 1) * S / (64 * NW));
   for (int pass = 0; pass < 2; ++pass) {
-    if (t < 64) {
+    if (t < 64 * NW) {
       SlicePart run[kRunRegs];
 #pragma unroll
-      for (int j = 0; j < kRunRegs; ++j) run[j] = slo + j < shi ? part(slo + j) : SlicePart{0.0, 0.0, 0.0, 0.0};
-      // every partial of the run in slice order
-      auto each = [&](auto&& f) {
+      for (int j = 0; j < kRunRegs; ++j) {
+        const int s = slo + j;
+        run[j] = s < shi ? SlicePart{part(s, PartEt()), part(s, PartEd()), part(s, PartQ()), part(s, PartQd())}
+                         : SlicePart{0.0, 0.0, 0.0, 0.0};
+      }
+      // two fields of every partial of the run, in slice order
+      auto each = [&](auto fa, auto fb, auto&& f) {
 #pragma unroll
         for (int j = 0; j < kRunRegs; ++j)
-          if (slo + j < shi) f(slo + j, run[j]);
-        for (int s = slo + kRunRegs; s < shi; ++s) f(s, part(s));
+          if (slo + j < shi) f(slo + j, field(run[j], fa), field(run[j], fb));
+        if constexpr (LONG) {
+          for (int s = slo + kRunRegs; s < shi; s += kRunStep) {
+            double pa[kRunStep], pb[kRunStep];
+#pragma unroll
+            for (int j = 0; j < kRunStep; ++j) {
+              const int sj = s + j < shi ? s + j : shi - 1;
+              pa[j] = part(sj, fa);
+              pb[j] = part(sj, fb);
+            }
+#pragma unroll
+            for (int j = 0; j < kRunStep; ++j)
+              if (s + j < shi) f(s + j, pa[j], pb[j]);
+          }
+        }
       };
       // fresh normalisers and the exact ratio
       double rho = 0.0;
       if (resid) {
         double te = 0.0, td = 0.0;
-        each([&](int, const SlicePart& p) {
-          te += p.et;
-          td += p.ed;
+        each(PartEt(), PartEd(), [&](int, double et, double ed) {
+          te += et;
+          td += ed;
         });
-        rho = wave_all_d(te, OpSumD()) / wave_all_d(td, OpSumD());
+        te = search_sum<NW>(te, s_v);
+        rho = te / search_sum<NW>(td, s_v);
       }
       // slice masses: first-order correction of the rho0 sums, or the target row's own
-      auto mass = [&](const SlicePart& p, bool rs) -> double {
-        if (!rs) return p.et;
-        const double m = p.q - (rho - (double)rho0) * p.qd;
-        return m > 0.0 ? m : 0.0;
+      auto masses = [&](bool rs, auto&& f) {
+        if (rs)
+          each(PartQ(), PartQd(), [&](int s, double q, double qd) {
+            const double m = q - (rho - (double)rho0) * qd;
+            f(s, m > 0.0 ? m : 0.0);
+          });
+        else
+          each(PartEt(), PartNone(), [&](int s, double et, double) { f(s, et); });
       };
       double sm = 0.0;
-      unsigned long long pos = 0;
+      int tlast = -1;
       bool rs = resid;
       for (;;) {
         sm = 0.0;
-        each([&](int, const SlicePart& p) { sm += mass(p, rs); });
-        pos = __ballot(sm > 0.0);
-        if (pos != 0ull || !rs) break;
+        masses(rs, [&](int, double m) { sm += m; });
+        tlast = search_thread<NW, true>(__ballot(sm > 0.0), s_b);
+        if (tlast >= 0 || !rs) break;
         rs = false;  // no residual mass: sample from the target row
       }
-      const double excl = dpp_d<0x138>(wave_incl_scan(sm)), end = excl + sm;
-      const int tlast = pos ? 63 - __builtin_clzll(pos) : 0;
-      const double x = (double)u * rl_d(end, tlast);
-      const unsigned long long over = __ballot(sm > 0.0 && end > x);
-      if (t == (over ? __builtin_ctzll(over) : tlast)) {
+      const double incl = wave_incl_scan(sm);
+      double excl = dpp_d<0x138>(incl);  // wave_shr:1, 0 into lane 0
+      if constexpr (NW > 1) {
+        share_waves<NW>(rl_d(incl, 63), s_v);
+        double before = 0.0;
+        for (int i = 0; i < (t >> 6); ++i) before += s_v[i];
+        excl = before + excl;
+      }
+      const double end = excl + sm;
+      double x;
+      if constexpr (NW == 1) {
+        x = (double)u * rl_d(end, tlast < 0 ? 0 : tlast);
+      } else {
+        if (t == (tlast < 0 ? 0 : tlast)) s_end = end;
+        __syncthreads();
+        x = (double)u * s_end;
+      }
+      const int tover = search_thread<NW, false>(__ballot(sm > 0.0 && end > x), s_b);
+      if (t == (tover >= 0 ? tover : (tlast < 0 ? 0 : tlast))) {
         // the slice inside this lane's run, repeating its sequential sums exactly
         double Pacc = 0.0, sbase = 0.0;
         int sstar = -1;
         bool done = false;
-        each([&](int s, const SlicePart& p) {
-          const double m = mass(p, rs);
+        masses(rs, [&](int s, double m) {
           const double Pn = Pacc + m;
           if (!done && m > 0.0) {
             sstar = s;
             sbase = excl + Pacc;
-            done = over != 0ull && excl + Pn > x;
+            done = tover >= 0 && excl + Pn > x;
           }
           Pacc = Pn;
         });
@@ -1779,7 +1875,7 @@ __device__ __forceinline__ void sample_from_parts(const T* trow, const T* drow, 
   if (t == 0) *out = -1;
 }
 
-template <typename T, Src SRC>
+template <typename T, Src SRC, bool LONG>
 __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S, const SlicePart* __restrict__ ws) {
   constexpr int BD = kSampleBD;
   __shared__ SampleLds s_l;
@@ -1787,10 +1883,11 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
   const int t = threadIdx.x;
   const int b = blockIdx.x;
   if (b >= a.B) return;
-  // the first slice partial of each lane of wave 0, written by k_final_parts: its load does
-  // not wait for the decisions, so the two round trips overlap (unused for an invalid
+  // the first slice partial of each searching thread, written by k_final_parts: its load
+  // does not wait for the decisions, so the two round trips overlap (unused for an invalid
   // sequence and in GREEDY mode, where no partials were written; inside the workspace)
-  const int slo = (int)((int64_t)t * S / 64), shi = t < 64 ? (int)((int64_t)(t + 1) * S / 64) : 0;
+  constexpr int NT = LONG ? BD : 64;
+  const int slo = (int)((int64_t)t * S / NT), shi = t < NT ? (int)((int64_t)(t + 1) * S / NT) : 0;
   const SlicePart first = slo < shi ? ws[(int64_t)b * S + slo] : SlicePart{0.0, 0.0, 0.0, 0.0};
   const SeqInfo q = SRC == Src::Record ? *pass_info(a, b) : seq_info(a, b, &s_q);
   if (SRC == Src::Record && (q.nacc < 0 || a.mode == CMSD_MODE_GREEDY)) return;  // written by k_pass_decide
@@ -1814,8 +1911,8 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
   const T* drow = reinterpret_cast<const T*>(a.draft) + q.dr * a.dstride;
   const float u = a.unif[q.off + q.kb];
   if (t == 0) a.n_acc[b] = nacc;
-  sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b,
-                           [&](int s) { return s == slo ? first : ws[(int64_t)b * S + s]; });
+  sample_from_parts<T, BD, LONG>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b,
+                                 [&](int s, auto f) { return s == slo ? field(first, f) : field(ws[(int64_t)b * S + s], f); });
 }
 
 // Both in one launch, for small launches: SW workgroups of kFinalWaves waves per sequence.
@@ -1837,7 +1934,7 @@ __device__ __forceinline__ int* final_count(const VerifyArgs& a, int b) {
   return reinterpret_cast<int*>(&a.pslots[(int64_t)b * (a.k_max + 1) + a.k_max].zd);
 }
 
-template <typename T, Src SRC>
+template <typename T, Src SRC, bool LONG>
 __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW, SlicePart* __restrict__ ws) {
   constexpr int BD = kFinalBD;
   __shared__ SampleLds s_l;
@@ -1883,9 +1980,9 @@ __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW,
   __syncthreads();
   if (s_done != SW - 1) return;
   const float u = a.unif[q.off + q.kb];
-  sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b, [&](int s) {
-    const double* p = reinterpret_cast<const double*>(P + s);
-    return SlicePart{ld_agent(p), ld_agent(p + 1), ld_agent(p + 2), ld_agent(p + 3)};
+  sample_from_parts<T, BD, LONG>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b, [&](int s, auto f) {
+    if constexpr (f < 0) return 0.0;
+    else return ld_agent(reinterpret_cast<const double*>(P + s) + f);
   });
 }
 
@@ -1953,8 +2050,11 @@ __device__ __forceinline__ void fused_tail(const VerifyArgs& a, int b, int S, Sl
   __syncthreads();  // the partials of every slice, written by this workgroup
   const float u = a.unif[q.off + q.kb];
   if (t == 0) a.n_acc[b] = q.nacc;
-  sample_from_parts<T, BD>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b,
-                           [&](int s) { return P[s]; });
+  auto part = [&](int s, auto f) { return field(P[s], f); };
+  if (S <= kShortSlices)
+    sample_from_parts<T, BD, false>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b, part);
+  else
+    sample_from_parts<T, BD, true>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b, part);
 }
 
 template <typename T>
@@ -2014,7 +2114,7 @@ __global__ __launch_bounds__(kPartBD) void k_draft_parts(const T* __restrict__ l
   }
 }
 
-template <typename T>
+template <typename T, bool LONG>
 __global__ __launch_bounds__(kSampleBD) void k_draft_pick(const T* __restrict__ logits, int64_t stride, int64_t V,
                                                           const cmsd_row_stats* __restrict__ stats,
                                                           const float* __restrict__ unif, int S,
@@ -2023,8 +2123,8 @@ __global__ __launch_bounds__(kSampleBD) void k_draft_pick(const T* __restrict__ 
   __shared__ SampleLds s_l;
   const int64_t r = blockIdx.x;
   const T* row = logits + r * stride;
-  sample_from_parts<T, BD>(row, row, V, false, stats[r].max_logit * kLog2e, 0.f, 0.f, unif[r], S, s_l, out + r,
-                           [&](int s) { return ws[r * S + s]; });
+  sample_from_parts<T, BD, LONG>(row, row, V, false, stats[r].max_logit * kLog2e, 0.f, 0.f, unif[r], S, s_l, out + r,
+                                 [&](int s, auto f) { return field(ws[r * S + s], f); });
 }
 
 // The same in one launch for rows of up to kDraftRowSlices slices (128 KB), one workgroup
@@ -2059,8 +2159,8 @@ __global__ __launch_bounds__(kDraftRowBD) void k_draft_row(const T* __restrict__
     }
   }
   __syncthreads();
-  sample_from_parts<T, BD>(row, row, V, false, mst, 0.f, 0.f, u, S, s_l, out + r,
-                           [&](int s) { return SlicePart{s_part[s], 0.0, 0.0, 0.0}; });
+  sample_from_parts<T, BD, false>(row, row, V, false, mst, 0.f, 0.f, u, S, s_l, out + r,
+                              [&](int s, auto f) { return f == 0 ? s_part[s] : 0.0; });
 }
 
 // ----------------------------------------------------------------------------- host helpers
@@ -2116,8 +2216,7 @@ int row_block(int64_t n_rows, int64_t row_bytes) {
 // drafter rows of 32000; 8 where a row is over 128 KB, for the confidence pass and the
 // joint pass of fp32 (two rounds -> three, us: 2048 fp32 drafter rows of 128256
 // 155.0 -> 153.5, 4096 of them 320.3 -> 315.1, 8192 bf16 ones 326.7 -> 318.5, 2040 fp32
-// rows of the joint pass 163.7 -> 161.9, 3400 of 50257 114.4 -> 109.7).  cmsd_verify's packed
-// target rows take three from 8 per unit on where a row is over 256 KB of fp32 (1700 of
+// rows of the joint pass 163.7 -> 161.9, 3400 of 50257 114.4 -> 109.7).  cmsd_verify's packed target rows take three from 8 per unit on where a row is over 256 KB of fp32 (1700 of
 // 128256 134.7 -> 133.0, 4352 of them 344.4 -> 338.4; of 40000 logits, 160 KB,
 // 110.9 -> 113.7; 3097 bf16 rows of 32000 slower too).  The depth only schedules loads: the
 // arithmetic, and so every result, is the same.  cmsd_set_row_shape forces it.
@@ -2328,26 +2427,36 @@ cmsd_status bind_pass_workspace(VerifyArgs& a, void* workspace, size_t workspace
 template <typename T, Src SRC>
 void launch_final(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
   const int SW = (S + kFinalWaves - 1) / kFinalWaves;
-  hipLaunchKernelGGL((k_final<T, SRC>), dim3((unsigned)(a.B * SW)), dim3(kFinalBD), 0, st, a, S, SW, ws);
+  const auto kernel = S <= kShortSlices ? k_final<T, SRC, false> : k_final<T, SRC, true>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(a.B * SW)), dim3(kFinalBD), 0, st, a, S, SW, ws);
+}
+template <typename T, Src SRC>
+void launch_final_sample(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
+  const auto kernel = S <= kShortSlices ? k_final_sample<T, SRC, false> : k_final_sample<T, SRC, true>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)a.B), dim3(kSampleBD), 0, st, a, S, ws);
 }
 template <typename T, Src SRC>
 void launch_final_pair(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
   const int SW = (S + kSubPerWG - 1) / kSubPerWG;
   const unsigned gp = (unsigned)((int64_t)a.B * SW);
   hipLaunchKernelGGL((k_final_parts<T, SRC>), dim3(gp), dim3(kPartBD), 0, st, a, S, SW, ws);
-  hipLaunchKernelGGL((k_final_sample<T, SRC>), dim3((unsigned)a.B), dim3(kSampleBD), 0, st, a, S, ws);
+  launch_final_sample<T, SRC>(a, S, ws, st);
 }
 
 // Whether the final token of a launch of that many slices takes one launch (k_final, which
 // in cmsd_logit_pass also forms the decisions) or, in cmsd_logit_pass behind the decision
 // kernel, two: up to 20 slice waves per compute unit one is faster or as fast (figures at
-// k_final).  cmsd_set_pass_decisions forces cmsd_logit_pass to either (0 = chosen per call,
-// 1 = record and pair, 2 = one launch); a grid past the launch limit takes the pair.
+// k_final).  Rows of more than 512 slices take the pair: their partials, handed off past the
+// L2, take the one launch's last workgroup longer than a launch (one sequence of 4 drafts,
+// fp32, one launch against the pair, us: 600000 55.6 and 55.5, 1000000 82.5 and 81.3,
+// 4000000 308 and 297; bf16 1000000, 489 slices, 73.0 and 73.7).  cmsd_set_pass_decisions
+// forces cmsd_logit_pass to either (0 = chosen per call, 1 = record and pair, 2 = one
+// launch); a grid past the launch limit takes the pair.
 std::atomic<int> g_pass_decisions{0};
 bool one_final_launch(int64_t batch, int S, int forced) {
   if (!launch_fits(batch * ((S + kFinalWaves - 1) / kFinalWaves), kFinalBD)) return false;
   if (forced) return forced == 2;
-  return batch * S <= 20 * (int64_t)device_cus();
+  return S <= 2 * kShortSlices && batch * S <= 20 * (int64_t)device_cus();
 }
 
 // Timing events armed by cmsd_set_row_events for the next cmsd_logit_pass call of this
@@ -2400,7 +2509,7 @@ bool one_draft_launch(int64_t n_rows, int S) {
 template <typename T>
 void launch_verify_final(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
   if (a.mode == CMSD_MODE_GREEDY)
-    hipLaunchKernelGGL((k_final_sample<T, Src::Verify>), dim3((unsigned)a.B), dim3(kSampleBD), 0, st, a, S, ws);
+    launch_final_sample<T, Src::Verify>(a, S, ws, st);
   else if (one_final_launch(a.B, S, 0))
     launch_final<T, Src::Verify>(a, S, ws, st);
   else
@@ -2493,12 +2602,12 @@ cmsd_status cmsd_draft_sample(const void* logits, int32_t dtype, int64_t n_rows,
   if (dtype == CMSD_F32) {
     hipLaunchKernelGGL((k_draft_parts<float>), gp, dim3(kPartBD), 0, st, static_cast<const float*>(logits), row_stride,
                        vocab, stats, S, SW, ws);
-    hipLaunchKernelGGL((k_draft_pick<float>), gr, dim3(kSampleBD), 0, st, static_cast<const float*>(logits),
+    hipLaunchKernelGGL((S <= kShortSlices ? k_draft_pick<float, false> : k_draft_pick<float, true>), gr, dim3(kSampleBD), 0, st, static_cast<const float*>(logits),
                        row_stride, vocab, stats, uniforms, S, ws, drafted);
   } else {
     hipLaunchKernelGGL((k_draft_parts<Bf16>), gp, dim3(kPartBD), 0, st, static_cast<const Bf16*>(logits), row_stride,
                        vocab, stats, S, SW, ws);
-    hipLaunchKernelGGL((k_draft_pick<Bf16>), gr, dim3(kSampleBD), 0, st, static_cast<const Bf16*>(logits),
+    hipLaunchKernelGGL((S <= kShortSlices ? k_draft_pick<Bf16, false> : k_draft_pick<Bf16, true>), gr, dim3(kSampleBD), 0, st, static_cast<const Bf16*>(logits),
                        row_stride, vocab, stats, uniforms, S, ws, drafted);
   }
   return launched();

@@ -149,3 +149,29 @@ def test_draft_sample_launch_rule(cm, dtype, slices):
         want, slack = O.draft_sample(row.astype(np.float64), float(u[r]))
         t.decision(f"y[{r}]", int(two[r]), want, slack)
     t.assert_ok()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("slices", [256, 257, 1030, 1300])
+def test_draft_sample_long_rows(cm, dtype, slices):
+    # the most slices that one wave searches, and rows that every wave of the workgroup
+    # searches: runs of one or two slices a thread, one past its registers, a step past them
+    vec = 4 if dtype == "f32" else 8
+    dev = torch.device("cuda:0")
+    V = vec * (256 * slices - 2) + 1
+    g = np.random.default_rng(V)
+    z = g.normal(0, 3.0, (7, V)).astype(np.float32)
+    z[4:6] = -np.inf
+    z[4, V - 1], z[5, 0] = 1.0, 1.0                       # all mass on the last, the first token
+    z[6] = -np.inf
+    z[6, ::1024] = 0.0                                    # a token in every slice
+    stored = z if dtype == "f32" else W.bf16_bits_from_f32(z)
+    u = np.array([0.0, 1.0 - 2.0 ** -24, 0.5, 0.99999, 0.3, 0.7, 0.600001], dtype=np.float32)
+    x = Hn.to_device(stored, dtype, dev)
+    y = cm.cmsd_draft_sample(x, cm.cmsd_confidence(x), torch.from_numpy(u).to(dev))
+    torch.cuda.synchronize()
+    t = Hn.Tally()
+    for r in range(7):
+        want, slack = O.draft_sample(Hn.decode(stored[r], dtype), float(u[r]))
+        t.decision(f"V={V} y[{r}]", int(y[r]), want, slack)
+    t.assert_ok()

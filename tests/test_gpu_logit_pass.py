@@ -156,6 +156,32 @@ def test_final_launches_bitwise_equal(cm, dtype, slices):
         _run_case(cm, zd, zt, dr, u, B, K, V, dtype)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("slices", [256, 257, 1030])
+def test_long_rows_bitwise_equal(cm, dtype, slices):
+    # the same where one wave searches the most slices it does, and where the whole
+    # workgroup does, from its registers and past them; the one-launch pass searches alike
+    vec = 4 if dtype == "f32" else 8
+    V, B, K = vec * (256 * slices - 2) + 1, 3, 2
+    g = np.random.default_rng(V)
+    zd, zt, dr, u = _case(g, B, K, V, dtype)
+    y = (int(np.argmax(Hn.decode(zd[K], dtype))) + 1) % V  # sequence 1: equal rows that mask the
+    zd[K, y] = 0xFF80 if dtype == "bf16" else -np.inf      # first draft, so no residual
+    zt[K + 1], dr[1, 0] = zd[K], y
+    dev = torch.device("cuda:0")
+    args = (Hn.to_device(zd, dtype, dev), Hn.to_device(zt, dtype, dev), torch.from_numpy(dr.reshape(-1)).to(dev),
+            torch.from_numpy(u.reshape(-1)).to(dev))
+    rec = _forced_decisions(cm, 1, lambda: _pass(cm, *args, B, K, O.MODE_STANDARD)[0])
+    one = _forced_decisions(cm, 2, lambda: _pass(cm, *args, B, K, O.MODE_STANDARD)[0])
+    fused = cm.cmsd_logit_pass_fused(*args, batch=B, k_max=K, mode=O.MODE_STANDARD, **Hn.PARAMS)
+    torch.cuda.synchronize()
+    for k in ("draft_stats", "draft_len", "target_stats", "n_accepted", "next_token"):
+        assert torch.equal(rec[k].view(torch.int32), one[k].view(torch.int32)), (V, k)
+        assert torch.equal(fused[k].view(torch.int32), one[k].view(torch.int32)), (V, k)
+    _, n_acc, _ = _run_case(cm, zd, zt, dr, u, B, K, V, dtype, mode=O.MODE_STANDARD)
+    assert n_acc[1] == 0
+
+
 def test_final_launch_rule_boundary(cm):
     # batches of one-slice vocabularies on either side of 20 slice waves per compute unit,
     # where the choice between one final-token launch and the pair falls: the same first
