@@ -2216,7 +2216,10 @@ int row_block(int64_t n_rows, int64_t row_bytes) {
 // drafter rows of 32000; 8 where a row is over 128 KB, for the confidence pass and the
 // joint pass of fp32 (two rounds -> three, us: 2048 fp32 drafter rows of 128256
 // 155.0 -> 153.5, 4096 of them 320.3 -> 315.1, 8192 bf16 ones 326.7 -> 318.5, 2040 fp32
-// rows of the joint pass 163.7 -> 161.9, 3400 of 50257 114.4 -> 109.7).  cmsd_verify's packed target rows take three from 8 per unit on where a row is over 256 KB of fp32 (1700 of
+// rows of the joint pass 163.7 -> 161.9, 3400 of 50257 114.4 -> 109.7); the joint pass of rows
+// over 384 KB takes three in every launch (one sequence of 4 drafts at fp32 128256
+// 16.3 -> 15.7, 200000 21.1 -> 20.0, 1000000 74.6 -> 73.2, 56 of 300000 90.9 -> 90.3; at bf16
+// 200000 19.7 -> 19.0, 1000000 68.1 -> 64.1).  cmsd_verify's packed target rows take three from 8 per unit on where a row is over 256 KB of fp32 (1700 of
 // 128256 134.7 -> 133.0, 4352 of them 344.4 -> 338.4; of 40000 logits, 160 KB,
 // 110.9 -> 113.7; 3097 bf16 rows of 32000 slower too).  The depth only schedules loads: the
 // arithmetic, and so every result, is the same.  cmsd_set_row_shape forces it.
@@ -2298,7 +2301,8 @@ void launch_row_pass_d(int bd, const VerifyArgs& a, int64_t rows, hipStream_t st
 }
 template <typename T>
 void launch_row_pass(int bd, const VerifyArgs& a, int64_t rows, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-  if (deep_ring(rows, std::is_same<T, float>::value && a.V * (int64_t)sizeof(T) > kLongRow ? 8 : 16))
+  const int64_t row_bytes = a.V * (int64_t)sizeof(T);
+  if (deep_ring(rows, row_bytes > 3 * kLongRow ? 0 : std::is_same<T, float>::value && row_bytes > kLongRow ? 8 : 16))
     launch_row_pass_d<T, CMSD_DEEP_DEPTH>(bd, a, rows, st, e0, e1);
   else
     launch_row_pass_d<T, CMSD_STREAM_DEPTH>(bd, a, rows, st, e0, e1);
