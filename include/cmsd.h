@@ -404,15 +404,16 @@ cmsd_status cmsd_logit_pass_noalloc(const void* draft_logits, int64_t draft_stri
 cmsd_status cmsd_set_row_shape(int32_t threads, int32_t ring_depth);
 
 /*
- * cmsd_set_pass_decisions - where cmsd_logit_pass (and cmsd_logit_pass_noalloc) forms
- * each sequence's draft length and accept tests outside GREEDY mode, for tuning and
- * for tests that cover both launch sequences.  Process-wide; applies to calls made
- * after it returns.
- *   mode  0: chosen per call from the number of final-token workgroups (default);
- *         1: one decision wave per sequence writes a record the final-token kernels
- *            read (four launches);
- *         2: every workgroup of one final-token launch forms the decisions from the
- *            row results (two launches).
+ * cmsd_set_pass_decisions - how cmsd_logit_pass (and cmsd_logit_pass_noalloc) and
+ * cmsd_verify form the final token outside GREEDY mode, and where the former forms each
+ * sequence's draft length and accept tests, for tuning and for tests that cover every
+ * launch sequence.  Process-wide; applies to calls made after it returns.
+ *   mode  0: chosen per call from the number and size of the final-token workgroups
+ *            (default);
+ *         1: two final-token launches, in cmsd_logit_pass behind one decision wave per
+ *            sequence that writes a record they read (four launches, cmsd_verify three);
+ *         2: one final-token launch, whose every workgroup forms the decisions of
+ *            cmsd_logit_pass from the row results (two launches, as cmsd_verify).
  * Both run the same arithmetic: the outputs are bit-identical.
  * Errors: CMSD_ERR_ARG for any other mode.
  */

@@ -180,9 +180,10 @@ def cmsd_set_row_shape(threads: int = 0, ring_depth: int = 0) -> None:
 
 
 def cmsd_set_pass_decisions(mode: int = 0) -> None:
-    """Where cmsd_logit_pass forms each sequence's decisions: 0 chosen per call, 1 a
-    decision kernel's record (four launches), 2 in every workgroup of
-    one final-token launch (two launches).  Bit-identical outputs.  Process-wide."""
+    """How cmsd_logit_pass and cmsd_verify form the final token: 0 chosen per call, 1 two
+    launches (cmsd_logit_pass: behind a decision kernel's record, four in all), 2 one launch
+    (in cmsd_logit_pass every workgroup of it forms the decisions, two in all).
+    Bit-identical outputs.  Process-wide."""
     _check("cmsd_set_pass_decisions", _lib.cmsd_set_pass_decisions(int(mode)))
 
 

@@ -2454,8 +2454,8 @@ void launch_final_pair(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st
 // L2, take the one launch's last workgroup longer than a launch (one sequence of 4 drafts,
 // fp32, one launch against the pair, us: 600000 55.6 and 55.5, 1000000 82.5 and 81.3,
 // 4000000 308 and 297; bf16 1000000, 489 slices, 73.0 and 73.7).  cmsd_set_pass_decisions
-// forces cmsd_logit_pass to either (0 = chosen per call, 1 = record and pair, 2 = one
-// launch); a grid past the launch limit takes the pair.
+// forces cmsd_logit_pass and cmsd_verify to either (0 = chosen per call, 1 = the pair, 2 =
+// one launch); a grid past the launch limit takes the pair.
 std::atomic<int> g_pass_decisions{0};
 bool one_final_launch(int64_t batch, int S, int forced) {
   if (!launch_fits(batch * ((S + kFinalWaves - 1) / kFinalWaves), kFinalBD)) return false;
@@ -2514,7 +2514,7 @@ template <typename T>
 void launch_verify_final(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st) {
   if (a.mode == CMSD_MODE_GREEDY)
     launch_final_sample<T, Src::Verify>(a, S, ws, st);
-  else if (one_final_launch(a.B, S, 0))
+  else if (one_final_launch(a.B, S, g_pass_decisions.load(std::memory_order_relaxed)))
     launch_final<T, Src::Verify>(a, S, ws, st);
   else
     launch_final_pair<T, Src::Verify>(a, S, ws, st);

@@ -21,6 +21,18 @@ def mods():
     return cmsd, pipeline
 
 
+@pytest.fixture(params=[0, 1], ids=["chosen", "pair"], autouse=True)
+def _final_launches(request):
+    # every test twice: the launches that the library chooses (one for the final token of
+    # all but the largest problems here), and the final-token pair forced
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_15371_amd import cmsd
+    cmsd.cmsd_set_pass_decisions(request.param)
+    yield
+    cmsd.cmsd_set_pass_decisions(0)
+
+
 def _params(pipeline, mode):
     P = Hn.PARAMS
     return pipeline.Params(lambdas=P["lambdas"], beta_margin=P["beta_margin"], k_min=P["k_min"], alpha=P["alpha"],
@@ -209,6 +221,33 @@ def test_random_ragged_problems(mods, seed):
         Hn.check_sequence(t, b, ztr, zdr, drafted[b], unif[off[b]:off[b] + kb + 1], C, kb, mode, P,
                           ts, int(off[b]), int(n_acc[b]), int(nxt[b]))
     t.assert_ok()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("slices", [1, 4, 5, 9, 257])
+def test_final_launches_bitwise_equal(mods, dtype, slices):
+    # one final-token launch and the pair, at the edges of a slice (256 units of 16 bytes),
+    # of a workgroup's four slices and of the one-wave search, an invalid sequence among
+    # ragged ones: the same bits
+    cmsd, _ = mods
+    vec = 4 if dtype == "f32" else 8
+    for units in (-1, 0, 1):
+        V, B, K = vec * (256 * slices - 2 + units), 4, 3
+        g = np.random.default_rng(V)
+        zd, zt_pad, drafted, unif_pad = _small_case(g, B, K, V, dtype)
+        drafted[2, 0] = V
+        k = np.array([3, 0, 2, 1], dtype=np.int32)
+        zt = W.pack_ragged(k, K, zt_pad.reshape(B, K + 1, V))
+        unif = W.pack_ragged(k, K, unif_pad.reshape(B, K + 1, 1)).reshape(-1)
+        got = []
+        for forced in (1, 2):
+            cmsd.cmsd_set_pass_decisions(forced)
+            got.append(_run_small(mods, zd, zt, drafted, unif, k, dtype, B, K, V)[1:])
+        (na, nt, ts), (na2, nt2, ts2) = got
+        assert na[2] == -1 and nt[2] == -1 and (np.delete(na, 2) >= 0).all()
+        assert np.array_equal(na, na2) and np.array_equal(nt, nt2)
+        for f in ts:
+            assert ts[f].tobytes() == ts2[f].tobytes(), f
 
 
 @pytest.mark.parametrize("block", [64, 128, 256])
