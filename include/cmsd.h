@@ -253,7 +253,7 @@ cmsd_status cmsd_verify(const void* draft_logits, int64_t draft_stride, const cm
  * the drafter and target rows together (they do not depend on each other), then the
  * final token.  Each sequence's draft length and accept tests are formed either by
  * every workgroup of one final-token launch from the row results (launches of at most
- * 20 final-token waves per compute unit) or by one wave per sequence ahead of two
+ * 5 final-token workgroups per compute unit, rows of at most 512 slices) or by one wave per sequence ahead of two
  * final-token launches (larger ones); cmsd_set_pass_decisions forces either.
  * In GREEDY mode, whose final token is the row's top token, the decision wave ends
  * the call.

@@ -1921,11 +1921,9 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
 // k_final_sample's order, so the outputs are the same bits).  The row pass before set the
 // count to zero.  Workgroup 0 of a sequence also writes what the decisions decide.  Bound
 // by its chain of memory round trips; us, MI355X, against the pair (V, sequences, bf16):
-// 32000 x 1 12.4 -> 10.0, 32000 x 8 13.5 -> 11.0, 50257 x 64 18.4 -> 16.0, 152064 x 64 (19
-// slice waves per compute unit) 24.3 -> 24.9 and a launch less; then the counting and the waits of resident
-// workgroups cost more than a launch: 32000 x 512 (32 per unit) 24.5 -> 31, 128256 x 256
-// (63 per unit) 37 -> 49.  Workgroups of 1, 2, 4 and 8 waves: 11.3, 10.6, 10.0 and 11.9 at
-// 32000 x 1, 18.3, 17.2, 16.0 and 15.9 at 50257 x 64.
+// 32000 x 1 12.4 -> 10.0, 32000 x 8 13.5 -> 11.0, 50257 x 64 18.4 -> 16.0 (where one launch
+// stops paying: one_final_launch).  Workgroups of 1, 2, 4 and 8 waves: 11.3, 10.6, 10.0 and
+// 11.9 at 32000 x 1, 18.3, 17.2, 16.0 and 15.9 at 50257 x 64.
 constexpr int kFinalWaves = 4;
 constexpr int kFinalBD = 64 * kFinalWaves;
 template <Src SRC>
@@ -2447,20 +2445,36 @@ void launch_final_pair(const VerifyArgs& a, int S, SlicePart* ws, hipStream_t st
   launch_final_sample<T, SRC>(a, S, ws, st);
 }
 
-// Whether the final token of a launch of that many slices takes one launch (k_final, which
-// in cmsd_logit_pass also forms the decisions) or, in cmsd_logit_pass behind the decision
-// kernel, two: up to 20 slice waves per compute unit one is faster or as fast (figures at
-// k_final).  Rows of more than 512 slices take the pair: their partials, handed off past the
-// L2, take the one launch's last workgroup longer than a launch (one sequence of 4 drafts,
-// fp32, one launch against the pair, us: 600000 55.6 and 55.5, 1000000 82.5 and 81.3,
-// 4000000 308 and 297; bf16 1000000, 489 slices, 73.0 and 73.7).  cmsd_set_pass_decisions
-// forces cmsd_logit_pass and cmsd_verify to either (0 = chosen per call, 1 = the pair, 2 =
-// one launch); a grid past the launch limit takes the pair.
+// Whether the final token of a launch takes one launch (k_final, which in cmsd_logit_pass
+// also forms the decisions) or, in cmsd_logit_pass behind the decision kernel, two.  One,
+// as long as all its workgroups are resident: five of four waves per compute unit, counted
+// as launched (a row of five slices takes two workgroups).  Waiting workgroups cost more
+// than the launches saved.  One launch over the pair, time of the whole call (k_pass_decide
+// in the pair's), at launched waves per compute unit of
+//     slices per row         12     20     24     28     32
+//     1   cmsd_logit_pass  0.87   0.90   1.04          1.01    (10, not 12, for 1 to 5)
+//         cmsd_verify      0.91   0.89   1.13          1.04
+//     4   cmsd_logit_pass  0.87   0.89   0.99          0.95
+//         cmsd_verify      0.88   0.90   1.00          0.92
+//     5   cmsd_logit_pass  0.91   0.96   1.08          1.09
+//         cmsd_verify      0.95   1.00   1.19          1.24
+//     16  cmsd_logit_pass  0.89   0.92   1.00   1.01   0.98
+//         cmsd_verify      0.91   0.94   1.03   1.07   1.04
+//     75  cmsd_logit_pass  0.94   0.97   1.00   1.00   1.01
+//         cmsd_verify      0.95   0.96   1.00   1.00   1.02
+// (us: 51 and 55 at 320 sequences of 16 slices and 4 drafts, 41 and 39 at 768 of 5.)
+// Rows of more than 512 slices take the pair: their partials, handed off past the L2, take
+// the one launch's last workgroup longer than a launch (one sequence of 4 drafts, fp32, one
+// launch against the pair, us: 600000 55.6 and 55.5, 1000000 82.5 and 81.3, 4000000 308 and
+// 297; bf16 1000000, 489 slices, 73.0 and 73.7).  cmsd_set_pass_decisions forces
+// cmsd_logit_pass and cmsd_verify to either (0 = chosen per call, 1 = the pair, 2 = one
+// launch); a grid past the launch limit takes the pair.
 std::atomic<int> g_pass_decisions{0};
 bool one_final_launch(int64_t batch, int S, int forced) {
-  if (!launch_fits(batch * ((S + kFinalWaves - 1) / kFinalWaves), kFinalBD)) return false;
+  const int64_t groups = batch * ((S + kFinalWaves - 1) / kFinalWaves);
+  if (!launch_fits(groups, kFinalBD)) return false;
   if (forced) return forced == 2;
-  return S <= 2 * kShortSlices && batch * S <= 20 * (int64_t)device_cus();
+  return S <= 2 * kShortSlices && groups <= 5 * (int64_t)device_cus();
 }
 
 // Timing events armed by cmsd_set_row_events for the next cmsd_logit_pass call of this

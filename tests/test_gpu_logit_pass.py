@@ -119,7 +119,7 @@ def _forced_decisions(cm, mode_forced, fn):
 @pytest.mark.parametrize("mode", [O.MODE_STANDARD, O.MODE_CM, O.MODE_GREEDY])
 @pytest.mark.parametrize("name", ["c2", "c3", "c4"])
 def test_decision_paths_bitwise_equal(cm, name, mode, adaptive):
-    # the decisions formed in every final-token workgroup (three launches) and read from
+    # the decisions formed in every final-token workgroup (two launches) and read from
     # the decision kernel's record (four launches) are the same arithmetic: bit-equal
     # outputs; c2 and c3 choose the first by default, c4 the second
     cfg = W.CONFIGS[name]
@@ -182,12 +182,15 @@ def test_long_rows_bitwise_equal(cm, dtype, slices):
     assert n_acc[1] == 0
 
 
-def test_final_launch_rule_boundary(cm):
-    # batches of one-slice vocabularies on either side of 20 slice waves per compute unit,
-    # where the choice between one final-token launch and the pair falls: the same first
-    # sequences, the same outputs
-    n = 20 * torch.cuda.get_device_properties(0).multi_processor_count
-    V, K, B = 64, 1, n + 1
+@pytest.mark.parametrize("vocab,per_cu", [(64, 5), (64, 20), (4100, 5), (4200, 2)])
+def test_final_launch_rule_boundary(cm, vocab, per_cu):
+    # batches of rows of one, five and five slices on either side of five final-token
+    # workgroups per compute unit, where the choice between one launch and the pair falls,
+    # and both past it: the same first sequences, the same outputs
+    n = per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    if vocab == 4200:
+        n += torch.cuda.get_device_properties(0).multi_processor_count // 2   # two workgroups each
+    V, K, B = vocab, 1, n + 1
     g = np.random.default_rng(3)
     dev = torch.device("cuda:0")
     dd = torch.from_numpy(g.normal(0, 2, (B * K, V)).astype(np.float32)).to(dev)
