@@ -370,13 +370,14 @@ __device__ __forceinline__ void block_sum_n(double (&v)[N], double* lds) {
 // round is free, and the addresses cost no vector instruction.  prep() runs once
 // the first loads are issued (work that must precede the first round overlaps their latency);
 // consume(raw[U], k, last) is called in round order, `last` (std::true_type) for the
-// rounds that may be partial.  Against pointer loads with a guarded partial round behind
+// rounds that may be partial.  With SHORT, a row of a single round requests its own vectors
+// only (16 fp32 drafter rows of 1000 4.5 -> 4.2 us, 65536 of them 150 -> 146).  Against pointer loads with a guarded partial round behind
 // the ring: 136 bf16 rows of 32000 8.9 -> 7.8 us, 128 fp32 ones 10.2 -> 8.5, 3334 packed
 // target rows 41.4 -> 37.7, 8448 fp32 rows of 128256 616.5 -> 614.
 #ifndef CMSD_STREAM_DEPTH
 #define CMSD_STREAM_DEPTH 2
 #endif
-template <int U, int BD, int DEPTH, typename P, typename F>
+template <int U, int BD, int DEPTH, bool SHORT, typename P, typename F>
 __device__ __forceinline__ void stream_rounds(const uint4* vp, int64_t nvec, int t, P&& prep, F&& consume) {
   const int n = int(nvec), nt = (n + U * BD - 1) / (U * BD);  // a row: under 2^29 vectors
   if (nt <= 0) {
@@ -384,6 +385,12 @@ __device__ __forceinline__ void stream_rounds(const uint4* vp, int64_t nvec, int
     return;
   }
   uint4 buf[DEPTH][U];
+  if (SHORT && nt == 1) {  // one round, and of that only what the row has
+    load_round<U, BD, true>(vp, n, 0, t, buf[0]);
+    prep();
+    consume(buf[0], 0, std::true_type());
+    return;
+  }
   auto refill = [&](int d, int k) {
     load_round<U, BD>(vp, n, k, t, buf[d]);
     __builtin_amdgcn_sched_barrier(0);  // rounds leave in order, before the next one is consumed
@@ -504,7 +511,11 @@ __device__ __forceinline__ void conf_one(ConfState& s, float z, int cid) {
 // if `kept`, else read again: nothing else of the workgroup runs meanwhile, so its U
 // loads all leave before any is looked at (a vector past the row reads the row's first
 // one, unused).  One at a time they were U dependent round trips (16 fp32 sequences of 8
-// drafts at V = 32000, GREEDY: target rows 12.2 -> 11.5 us).
+// drafts at V = 32000, GREEDY: target rows 12.2 -> 11.5 us).  A row of a few vectors per
+// thread takes them one at a time all the same: the code for all U, fetched anew by every
+// launch, takes longer than up to four trips of fp32 vectors or three of bf16 (16 drafter
+// rows, us, all at once and one at a time: fp32 1000 5.2 and 4.5, 4000 5.2 and 4.8; bf16 1000
+// 5.1 and 4.3, 6000 5.2 and 4.95, 8000 5.15 and 5.2).
 template <typename T, int BD>
 __device__ __forceinline__ void max_chunk(const T* row, const Geom& g, int64_t nr, int cid, float m, bool kept,
                                           const uint4 (&keep)[Elem<T>::U], int64_t& idx, float& other) {
@@ -519,11 +530,25 @@ __device__ __forceinline__ void max_chunk(const T* row, const Geom& g, int64_t n
     idx = g.head + g.nvec * VEC + t;
   } else if (cid > 0) {
     const int64_t j0 = (int64_t)(cid - 1) * U * BD + t;
+    const uint4* vp = reinterpret_cast<const uint4*>(row + g.head);
+    if (!kept && g.nvec <= (U == 8 ? 4 : 3) * BD) {  // short rows: a vector at a time
+#pragma unroll 1
+      for (int64_t j = j0; j < g.nvec; j += BD) {
+        float f[VEC];
+        E::unpack(vp[j], f);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          const bool first = idx == INT64_MAX && f[e] == m;
+          other = first ? other : fmaxf(other, f[e]);
+          idx = first ? g.head + j * VEC + e : idx;
+        }
+      }
+      return;
+    }
     uint4 v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = make_uint4(0u, 0u, 0u, 0u);
     if (!kept) {
-      const uint4* vp = reinterpret_cast<const uint4*>(row + g.head);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t j = j0 + (int64_t)u * BD;
@@ -634,7 +659,7 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
     // the last one, the tail first (the head then wins a tie for the row max)
     const int64_t tail0 = g.head + g.nvec * VEC;
     float hv = 0.f, tv = 0.f;
-    stream_rounds<U, BD, DEPTH>(vp, g.nvec, t, [&] {
+    stream_rounds<U, BD, DEPTH, !VAR>(vp, g.nvec, t, [&] {
       hv = E::load(row + (t < g.head ? t : 0));
       tv = E::load(row + (t < g.tail ? tail0 + t : 0));
     }, [&](uint4 (&raw)[U], int k, auto last) {
@@ -807,15 +832,14 @@ __device__ __forceinline__ void conf_row(const T* __restrict__ row, int64_t V, c
 // 128256 315.1 at 2, 317.3 at 3, 318.9 at 4; the 4352 target rows of cmsd_verify beside
 // them 338.4 at 2, 342.2 at 3, 344.7 at 4.
 #define CMSD_WAVES(W) __attribute__((amdgpu_waves_per_eu((W) ? (W) : 1, (W) ? (W) : 8)))
-template <typename T, int BD, bool VAR, int DEPTH>
-constexpr int kConfWaves = !std::is_same<T, Bf16>::value ? (DEPTH == 3 && BD == 256 ? 2 : 0)
-                           : VAR                         ? 0
-                           : DEPTH == 2                  ? (BD > 64 ? 6 : 0)
-                                                         : (BD == 128 ? 0 : 3);
-template <typename T, int BD, int DEPTH>
-constexpr int kTargetWaves = !std::is_same<T, Bf16>::value && DEPTH == 3 && BD == 256 ? 2 : 0;
 template <typename T, int BD, int DEPTH>
 constexpr int kRowWaves = BD == 64 ? 0 : std::is_same<T, Bf16>::value ? (DEPTH == 2 ? 6 : 3) : (DEPTH == 2 ? 5 : 2);
+template <typename T, int BD, bool VAR, int DEPTH>
+constexpr int kConfWaves = VAR ? (!std::is_same<T, Bf16>::value && DEPTH == 3 && BD == 256 ? 2 : 0)
+                           : BD == 64 ? (std::is_same<T, Bf16>::value && DEPTH == 3 ? 3 : 0)
+                                      : (BD == 128 && DEPTH == 3 ? 0 : kRowWaves<T, BD, DEPTH>);
+template <typename T, int BD, int DEPTH>
+constexpr int kTargetWaves = !std::is_same<T, Bf16>::value && DEPTH == 3 && BD == 256 ? 2 : 0;
 
 template <typename T, int BD, bool VAR, int DEPTH>
 __global__ __launch_bounds__(BD) CMSD_WAVES((kConfWaves<T, BD, VAR, DEPTH>)) void k_confidence(const T* __restrict__ logits, int64_t n_rows, int64_t V,
@@ -992,7 +1016,7 @@ __device__ __forceinline__ void target_stream(const T* row, const Geom& g, const
   // past them element 0); the head is folded in once prep() has waited for its own loads
   const int64_t tail0 = g.head + g.nvec * VEC;
   float tv = 0.f;
-  stream_rounds<U, BD, DEPTH>(
+  stream_rounds<U, BD, DEPTH, true>(
       vp, g.nvec, t,
       [&] {
         const float hv = E::load(row + (t < g.head ? t : 0));

@@ -27,7 +27,9 @@ constexpr int kBufferNt = 2;
 // 2^31 logits): the scalar unit has no 64-bit comparison.  The count of records is said to
 // be uniform, or the compiler clamps it in the vector unit and wraps every load in a loop
 // over the lanes' values (one fp32 row of a million 99.6 -> 71.6 us).
-template <int U, int BD>
+// SKIP: vectors that no thread has are not requested (a load past the records reads nothing,
+// but takes its turn in the memory pipeline all the same).
+template <int U, int BD, bool SKIP = false>
 __device__ __forceinline__ void load_round(const uint4* vp, int nvec, int k, int t, uint4 (&buf)[U]) {
   constexpr int kSpan = 4;
   static_assert(U % kSpan == 0, "whole descriptors");
@@ -40,6 +42,10 @@ __device__ __forceinline__ void load_round(const uint4* vp, int nvec, int k, int
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(vp) + first, 0, 16 * n, kBufferFlags);
 #pragma unroll
     for (int u = 0; u < kSpan; ++u) {
+      if (SKIP && u * BD >= n) {
+        buf[h + u] = make_uint4(0u, 0u, 0u, 0u);
+        continue;
+      }
       const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (u * BD + t) * 16, 0, kBufferNt);
       buf[h + u] = make_uint4(v.x, v.y, v.z, v.w);
     }
