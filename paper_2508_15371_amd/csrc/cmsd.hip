@@ -1943,7 +1943,7 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
 // Each forms the sequence's decisions, each of its waves sums one slice of the chosen row
 // (pair) and leaves the partials, and the workgroup that counts last samples from them (in
 // k_final_sample's order, so the outputs are the same bits).  The row pass before set the
-// count to zero.  Workgroup 0 of a sequence also writes what the decisions decide.  Bound
+// count to zero.  Workgroup 0 of a sequence also writes its lengths and row records.  Bound
 // by its chain of memory round trips; us, MI355X, against the pair (V, sequences, bf16):
 // 32000 x 1 12.4 -> 10.0, 32000 x 8 13.5 -> 11.0, 50257 x 64 18.4 -> 16.0 (where one launch
 // stops paying: one_final_launch).  Workgroups of 1, 2, 4 and 8 waves: 11.3, 10.6, 10.0 and
@@ -1966,11 +1966,13 @@ __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW,
   const int b = int(blockIdx.x / (unsigned)SW), part = int(blockIdx.x % (unsigned)SW);
   if (b >= a.B) return;
   const SeqInfo q = SRC == Src::Inline ? seq_info_pass(a, b, part == 0, &s_q) : seq_info(a, b, &s_q);
-  if (part == 0 && t == 0) {
-    a.n_acc[b] = q.nacc;
-    if (q.nacc < 0) a.next_tok[b] = -1;
+  if (q.nacc < 0) {
+    if (part == 0 && t == 0) {
+      a.n_acc[b] = -1;
+      a.next_tok[b] = -1;
+    }
+    return;
   }
-  if (q.nacc < 0) return;
   const bool resid = q.nacc < q.kb;
   const T* trow = reinterpret_cast<const T*>(a.target) + q.tr * a.tstride;
   const T* drow = reinterpret_cast<const T*>(a.draft) + q.dr * a.dstride;
@@ -2001,6 +2003,9 @@ __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW,
   if (t == 0) s_done = count_agent(final_count<SRC>(a, b));
   __syncthreads();
   if (s_done != SW - 1) return;
+  // only now: cmsd_verify's caller may have n_accepted in draft_len's place, which the
+  // sequence's other workgroups have read before they were counted
+  if (t == 0) a.n_acc[b] = q.nacc;
   const float u = a.unif[q.off + q.kb];
   sample_from_parts<T, BD, LONG>(trow, drow, a.V, resid, q.mst, q.msd, q.rho0, u, S, s_l, a.next_tok + b, [&](int s, auto f) {
     if constexpr (f < 0) return 0.0;

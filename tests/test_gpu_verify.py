@@ -345,6 +345,33 @@ def test_invalid_device_inputs_are_reported(mods):
     assert n_acc[B - 1] == -1 and (n_acc[: B - 1] >= 0).all()
 
 
+def test_n_accepted_in_draft_len_place(mods):
+    # a caller may take the accepted lengths in the buffer of the draft lengths: every
+    # workgroup of a sequence reads them before one writes, invalid sequences included
+    cmsd, _ = mods
+    g = np.random.default_rng(17)
+    B, K, V = 64, 5, 32001
+    zd, zt_pad, drafted, unif_pad = _small_case(g, B, K, V, "bf16")
+    k = g.integers(0, K + 1, B).astype(np.int32)
+    k[3], k[9] = 2, 4
+    drafted[3, 1] = V                                     # invalid: an id out of range
+    zt = W.pack_ragged(k, K, zt_pad.reshape(B, K + 1, V))
+    unif = W.pack_ragged(k, K, unif_pad.reshape(B, K + 1, 1)).reshape(-1)
+    off = np.concatenate([[0], np.cumsum(k + 1)]).astype(np.int32)
+    k[9] = K + 1                                          # invalid: a length out of range
+    dev = torch.device("cuda:0")
+    dd, td = Hn.to_device(zd, "bf16", dev), Hn.to_device(zt, "bf16", dev)
+    st = cmsd.cmsd_confidence(dd)
+    args = (torch.from_numpy(off).to(dev), torch.from_numpy(drafted.reshape(-1)).to(dev), torch.from_numpy(unif).to(dev))
+    ref = cmsd.cmsd_verify(dd, st, td, args[0], torch.from_numpy(k).to(dev), *args[1:], batch=B, k_max=K)
+    assert ref[0][3] == -1 and ref[0][9] == -1 and (ref[0] >= 0).sum() == B - 2
+    for _ in range(4):
+        kd = torch.from_numpy(k).to(dev)
+        got = cmsd.cmsd_verify(dd, st, td, args[0], kd, *args[1:], batch=B, k_max=K, n_accepted=kd)
+        torch.cuda.synchronize()
+        assert torch.equal(kd, ref[0]) and torch.equal(got[1], ref[1])
+
+
 def test_draft_len_edges(mods):
     cmsd, _ = mods
     dev = torch.device("cuda:0")
