@@ -12,6 +12,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 import re
+import warnings
 
 import torch
 
@@ -98,18 +99,20 @@ _lib = _load()
 
 # The native marshalling of the common case (csrc/binding.cpp): every tensor and number
 # given, of the plain type and fitting.  Its functions return None for anything else, which
-# then takes the Python marshalling below.  Host time of a call whose buffers are given,
-# enqueued back to back
-# on an MI355X host, us, Python -> native: cmsd_logit_pass 20.3 (three launches) -> 7.0 (two),
-# cmsd_logit_pass_fused 15.0 -> 4.5, cmsd_confidence_var 9.6 -> 3.5, the three calls of a
-# packed iteration in GREEDY mode 33.2 -> 13.4.
+# then takes the Python marshalling below, as every call does where the module is missing or
+# of another interpreter or torch.  Host time of a call whose buffers are given, enqueued
+# back to back on an MI355X host, us, Python -> native: cmsd_logit_pass 20.3 (three launches)
+# -> 7.0 (two), cmsd_logit_pass_fused 15.0 -> 4.5, cmsd_confidence_var 9.6 -> 3.5, the three
+# calls of a packed iteration in GREEDY mode 33.2 -> 13.4.
 try:
     from . import _binding as _native
     _native.bind(*(C.cast(getattr(_lib, f), C.c_void_p).value for f in (
         "cmsd_confidence", "cmsd_confidence_var", "cmsd_draft_len", "cmsd_draft_sample", "cmsd_verify",
         "cmsd_logit_pass", "cmsd_logit_pass_fused")))
-except ImportError:
+except ImportError as e:
     _native = None
+    warnings.warn(f"no native argument marshalling ({e}): small calls take 6 to 20 us more of host time; "
+                  "`python -m paper_2508_15371_amd.build` builds it", RuntimeWarning, stacklevel=2)
 
 
 def lib() -> C.CDLL:

@@ -1,8 +1,14 @@
 """The Python binding rejects caller buffers of the wrong dtype, layout or size
 before any device work (the C entry points take plain pointers and cannot check
 sizes).  CPU only: the checks run on tensor metadata."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 cm = pytest.importorskip("paper_2508_15371_amd.cmsd")
 
@@ -139,3 +145,41 @@ def test_native_marshalling_same_calls():
     for a, b in zip(native, plain):
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
     assert errs == plain_errs
+
+
+def test_build_without_a_host_compiler(tmp_path, monkeypatch):
+    # the native marshalling is optional: no compiler means a warning and no module, and
+    # not one of an earlier build either
+    from paper_2508_15371_amd import build as B
+    lib = tmp_path / "_binding.so"
+    lib.write_bytes(b"of an earlier build")
+    monkeypatch.setattr(B, "BINDING_LIB", str(lib))
+    monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    with pytest.warns(RuntimeWarning, match="not built"):
+        assert B.build_binding_if_possible() is False
+    assert not lib.exists()
+
+
+def test_missing_native_marshalling_is_said():
+    # a module that cannot be imported is not passed over silently, and calls still work
+    code = """
+import sys, warnings, torch
+class Block:
+    def find_spec(self, name, path=None, target=None):
+        if name.endswith("._binding"):
+            raise ImportError("of another torch")
+sys.meta_path.insert(0, Block())
+with warnings.catch_warnings(record=True) as w:
+    warnings.simplefilter("always")
+    from paper_2508_15371_amd import cmsd
+assert cmsd._native is None
+assert any("of another torch" in str(x.message) and x.category is RuntimeWarning for x in w), w
+try:
+    cmsd.cmsd_confidence(torch.zeros(4, 100), torch.zeros(4, 8))
+except ValueError as e:
+    assert "device" in str(e)
+else:
+    raise SystemExit("no error")
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
