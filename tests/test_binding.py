@@ -94,10 +94,27 @@ def test_native_marshalling_leaves_the_rest_to_python():
         n.bind(*[0] * 7)
 
 
+class _Recorder:
+    """The native module, with the answers of each of its functions kept."""
+
+    def __init__(self, native):
+        self._n, self.answers = native, {}
+
+    def __getattr__(self, name):
+        f = getattr(self._n, name)
+
+        def call(*args):
+            s = f(*args)
+            self.answers.setdefault(name, []).append(s)
+            return s
+        return call
+
+
 @pytest.mark.gpu
 def test_native_marshalling_same_calls():
-    # the same call through the native and the Python marshalling: equal outputs, and the
-    # same refusals (status and message) for misfitting device buffers
+    # the same call through the native and the Python marshalling: every well-formed call is
+    # the native one's case, equal outputs, and the same refusals (status and message) for
+    # misfitting device buffers
     dev = torch.device("cuda:0")
     B, K, V = 3, 4, 500
     g = torch.Generator().manual_seed(0)
@@ -124,7 +141,28 @@ def test_native_marshalling_same_calls():
                   target_stats=z(_f(B * (K + 1), 8)), n_accepted=z(_i(B)), next_token=z(_i(B)), workspace=w)
             got += [o[n] for n in ("draft_stats", "draft_len", "target_stats", "n_accepted", "next_token")]
             assert o["workspace"] is w
+        # GREEDY without uniforms, on a stream of the caller's
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        greedy = dict(batch=B, k_max=K, mode=cm.CMSD_MODE_GREEDY, stream=side)
+        gst, gts, gna, gnt = z(_f(B * K, 8)), z(_f(B * (K + 1), 8)), z(_i(B)), z(_i(B))
+        side.wait_stream(torch.cuda.current_stream())
+        cm.cmsd_confidence(dd, gst, stream=side)
+        cm.cmsd_verify(dd, gst, td, off, k, dr, None, target_stats=gts, n_accepted=gna, next_token=gnt, workspace=ws,
+                       **greedy)
+        got += [gst, gts, gna, gnt]
+        for f, w in ((cm.cmsd_logit_pass, ws), (cm.cmsd_logit_pass_fused, fws)):
+            o = dict(draft_stats=z(_f(B * K, 8)), draft_len=z(_i(B)), target_stats=z(_f(B * (K + 1), 8)),
+                     n_accepted=z(_i(B)), next_token=z(_i(B)))
+            side.wait_stream(torch.cuda.current_stream())
+            f(dd, td, dr, None, workspace=w, **o, **greedy)
+            got += list(o.values())
         torch.cuda.synchronize()
+        if isinstance(cm._native, _Recorder):
+            answers = dict(cm._native.answers)
+            assert set(answers) == {"confidence", "confidence_var", "draft_len", "draft_sample", "verify", "logit_pass",
+                                    "logit_pass_fused"}
+            assert all(s == cm.CMSD_OK for f in answers for s in answers[f]), answers
         errs = []
         for call in (lambda: cm.cmsd_confidence(dd, z(_f(2, 8))), lambda: cm.cmsd_confidence(dd.t(), st),
                      lambda: cm.cmsd_confidence(dd, st, beta_margin=-1.0),
@@ -136,9 +174,12 @@ def test_native_marshalling_same_calls():
             errs.append((type(e.value), str(e.value)))
         return got, errs
 
-    native, errs = outputs()
-    keep, cm._native = cm._native, None
+    keep = cm._native
+    assert keep is not None
     try:
+        cm._native = _Recorder(keep)
+        native, errs = outputs()
+        cm._native = None
         plain, plain_errs = outputs()
     finally:
         cm._native = keep
