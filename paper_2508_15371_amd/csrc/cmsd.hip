@@ -201,12 +201,14 @@ __device__ __forceinline__ uint4 select4(bool c, const uint4& a, const uint4& b)
 }
 
 // ----------------------------------------------------------------------------- hand-off inside a launch
-// Data that one workgroup leaves for another of the same launch.  Relaxed atomics at agent
-// scope go past the XCD's own L2, on both sides, so nothing has to be written back or
-// invalidated: the writer's stores have reached the point that every XCD sees once they
-// are acknowledged (the wait), and only then is its workgroup counted; the reader loads
-// after the count's return.  A device fence instead writes back the whole L2, 30 to 50 ns
-// of the chip per workgroup.
+// Data that one workgroup leaves for another of the same launch.  This rests on gfx950 and
+// not on the language's memory model, in which relaxed atomics order nothing: relaxed atomics
+// at agent scope go past the XCD's own L2 there, on both sides (the sc1 bit), so nothing has
+// to be written back or invalidated; the writer's stores have reached the point that every
+// XCD sees once they are acknowledged (the wait on the vector-memory counter, by every wave
+// that stored and before its barrier), and only then is its workgroup counted; the reader
+// loads after the count's return, on which its branch depends.  A device fence instead
+// writes back the whole L2, 30 to 50 ns of the chip per workgroup.
 __device__ __forceinline__ void st_agent(double* p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -269,7 +271,6 @@ struct OpMax { __device__ float operator()(float a, float b) const { return fmax
 struct OpSumD { __device__ double operator()(double a, double b) const { return a + b; } };
 struct OpSumI { __device__ int operator()(int a, int b) const { return a + b; } };
 struct OpMinI { __device__ int operator()(int a, int b) const { return a < b ? a : b; } };
-struct OpMaxI { __device__ int operator()(int a, int b) const { return a > b ? a : b; } };
 
 template <typename Op>
 __device__ __forceinline__ float wave_all_f(float v, Op op) {
@@ -308,18 +309,6 @@ __device__ __forceinline__ float block_all_f(float v, Op op, float* slot) {
   if ((threadIdx.x & 63) == 0) slot[threadIdx.x >> 6] = w;
   __syncthreads();
   float r = slot[0];
-#pragma unroll
-  for (int i = 1; i < NW; ++i) r = op(r, slot[i]);
-  return r;
-}
-template <int BD, typename Op>
-__device__ __forceinline__ double block_all_d(double v, Op op, double* slot) {
-  constexpr int NW = BD / 64;
-  const double w = wave_all_d(v, op);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) slot[threadIdx.x >> 6] = w;
-  __syncthreads();
-  double r = slot[0];
 #pragma unroll
   for (int i = 1; i < NW; ++i) r = op(r, slot[i]);
   return r;
@@ -842,11 +831,10 @@ template <typename T, int BD, int DEPTH>
 constexpr int kTargetWaves = !std::is_same<T, Bf16>::value && DEPTH == 3 && BD == 256 ? 2 : 0;
 
 template <typename T, int BD, bool VAR, int DEPTH>
-__global__ __launch_bounds__(BD) CMSD_WAVES((kConfWaves<T, BD, VAR, DEPTH>)) void k_confidence(const T* __restrict__ logits, int64_t n_rows, int64_t V,
-                                                   int64_t stride, ConfArgs a, cmsd_row_stats* __restrict__ out,
-                                                   float* __restrict__ var_out) {
+__global__ __launch_bounds__(BD) CMSD_WAVES((kConfWaves<T, BD, VAR, DEPTH>)) void k_confidence(
+    const T* __restrict__ logits, int64_t V, int64_t stride, ConfArgs a, cmsd_row_stats* __restrict__ out,
+    float* __restrict__ var_out) {
   const int64_t r = blockIdx.x;
-  if (r >= n_rows) return;
   conf_row<T, BD, VAR, DEPTH>(logits + r * stride, V, a, out + r, VAR ? var_out + r : nullptr);
 }
 
@@ -997,7 +985,7 @@ __device__ __forceinline__ void target_chunk(TargetState& s, const float* f, int
   }
   norm_chunk<N, false>(s.n, f, cmax);
   // keeps the sums of this chunk from sinking below the next one's branch, which had both
-  // rounds' logits in registers at once (108 -> 65 for 256-thread bf16 rows)
+  // rounds' logits in registers at once (108 -> 67 for 256-thread bf16 rows)
   asm volatile("" : "+v"(s.n.A), "+v"(s.n.ms));
 }
 
@@ -1088,7 +1076,6 @@ __device__ __forceinline__ void target_row(const VerifyArgs& a, int64_t q) {
   int kb = a.k_max, y = -1;
   cmsd_row_stats ds{};
   if (!PASS) {
-    if (b >= a.B) return;
     kb = a.klen[b];
     const int64_t ob = a.off[b], ob1 = a.off[b + 1];
     y = in_k ? a.drafted[drow] : -1;
@@ -1104,7 +1091,6 @@ __device__ __forceinline__ void target_row(const VerifyArgs& a, int64_t q) {
   // (cmsd_verify), so their latency hides behind the rounds'; in the single-call pass
   // the id load itself waits for the first rounds to be requested (prep()).
   bool valid = true, has_draft = false, count = false;
-  const bool layout = true;
   int yd = -1;
   float gz = -INFINITY, zd = -INFINITY, cm = 0.f, dm = 0.f, dA = 1.f;
   auto gather = [&] {
@@ -1191,7 +1177,7 @@ __device__ __forceinline__ void target_row(const VerifyArgs& a, int64_t q) {
                                top1, &res.n_greater);
     }
     a.tstats[r] = res;
-    if (layout) a.slots[(int64_t)b * (a.k_max + 1) + i] = RowSlot{m, (float)A, res.accept, (int32_t)r, top1, dm, dA, 0};
+    a.slots[(int64_t)b * (a.k_max + 1) + i] = RowSlot{m, (float)A, res.accept, (int32_t)r, top1, dm, dA, 0};
   }
 }
 
@@ -1484,7 +1470,6 @@ __device__ __forceinline__ SeqInfo* pass_info(const VerifyArgs& a, int b) {
 __global__ __launch_bounds__(64) void k_pass_decide(VerifyArgs a) {
   __shared__ SeqInfo s_q;
   const int b = blockIdx.x;
-  if (b >= a.B) return;
   const SeqInfo q = seq_info_pass(a, b, true, &s_q);
   if (threadIdx.x == 0) {
     *pass_info(a, b) = q;
@@ -1557,7 +1542,6 @@ __global__ __launch_bounds__(kPartBD) void k_final_parts(VerifyArgs a, int S, in
   __shared__ SeqInfo s_q;
   const int t = threadIdx.x;
   const int b = blockIdx.x / SW, sl0 = (blockIdx.x % SW) * kSubPerWG;
-  if (b >= a.B) return;
   const SeqInfo q = SRC == Src::Record ? *pass_info(a, b) : seq_info(a, b, &s_q);
   if (q.nacc < 0) return;
   const bool resid = q.nacc < q.kb;
@@ -1906,7 +1890,6 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
   __shared__ SeqInfo s_q;
   const int t = threadIdx.x;
   const int b = blockIdx.x;
-  if (b >= a.B) return;
   // the first slice partial of each searching thread, written by k_final_parts: its load
   // does not wait for the decisions, so the two round trips overlap (unused for an invalid
   // sequence and in GREEDY mode, where no partials were written; inside the workspace)
@@ -1914,7 +1897,7 @@ __global__ __launch_bounds__(kSampleBD) void k_final_sample(VerifyArgs a, int S,
   const int slo = (int)((int64_t)t * S / NT), shi = t < NT ? (int)((int64_t)(t + 1) * S / NT) : 0;
   const SlicePart first = slo < shi ? ws[(int64_t)b * S + slo] : SlicePart{0.0, 0.0, 0.0, 0.0};
   const SeqInfo q = SRC == Src::Record ? *pass_info(a, b) : seq_info(a, b, &s_q);
-  if (SRC == Src::Record && (q.nacc < 0 || a.mode == CMSD_MODE_GREEDY)) return;  // written by k_pass_decide
+  if (SRC == Src::Record && q.nacc < 0) return;  // written by k_pass_decide, as GREEDY's are
   if (q.nacc < 0) {
     if (t == 0) {
       a.n_acc[b] = -1;
@@ -1964,7 +1947,6 @@ __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW,
   __shared__ SeqInfo s_q;
   const int t = threadIdx.x;
   const int b = int(blockIdx.x / (unsigned)SW), part = int(blockIdx.x % (unsigned)SW);
-  if (b >= a.B) return;
   const SeqInfo q = SRC == Src::Inline ? seq_info_pass(a, b, part == 0, &s_q) : seq_info(a, b, &s_q);
   if (q.nacc < 0) {
     if (part == 0 && t == 0) {
@@ -2013,10 +1995,6 @@ __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW,
   });
 }
 
-// ----------------------------------------------------------------------------- K5 draft sampling
-// One exact softmax sample per drafter row (the draws a sampled draft needs):
-// vocabulary-slice partials of e = 2^(z log2e - m log2e), then the same slice scan
-// and exact in-slice locate as the final token, with u one uniform per row.
 // ----------------------------------------------------------------------------- fused pass (small batches)
 // The whole dense logit pass in one launch.  The grid is k_row_pass's (drafter rows,
 // then target rows, one 256-thread workgroup each).  Every row workgroup hands its record
@@ -2109,6 +2087,10 @@ __global__ __launch_bounds__(kFusedBD) void k_fused_pass(VerifyArgs a, int S, Sl
   fused_tail<T>(a, b, S, ws);
 }
 
+// ----------------------------------------------------------------------------- K5 draft sampling
+// One exact softmax sample per drafter row (the draws a sampled draft needs):
+// vocabulary-slice partials of e = 2^(z log2e - m log2e), then the same slice scan
+// and exact in-slice locate as the final token, with u one uniform per row.
 template <typename T>
 __global__ __launch_bounds__(kPartBD) void k_draft_parts(const T* __restrict__ logits, int64_t stride, int64_t V,
                                                          const cmsd_row_stats* __restrict__ stats, int S, int SW,
@@ -2260,10 +2242,9 @@ bool deep_ring(int64_t n_rows, int rows_per_cu) {
 
 // Rows per confidence launch: the launch's work-items (rows x threads) stay below 2^32,
 // and further rows go into further launches.  (A loop over rows inside the kernel had the
-// compiler keep the record's fp64 constants in registers across it: 152 instead of 120
-// registers for 256-thread bf16 rows, 245 instead of 144 for fp32, 204 instead of 136 for
-// the 64-thread rows of long launches.  One row per workgroup: 8192 masked rows of 32000
-// bf16 logits 88.9 -> 86.4 us, 128 fp32 rows of 32000 10.6 -> 10.1, 16 of them 8.7 -> 8.1.)
+// compiler keep the record's fp64 constants in registers across it, 30 to 100 of them: 8192
+// masked rows of 32000 bf16 logits 88.9 us with it and 86.4 without, 128 fp32 rows of 32000
+// 10.6 and 10.1, 16 of them 8.7 and 8.1.)
 constexpr int64_t kConfMaxGrid = (int64_t)1 << 22;
 
 template <typename T, bool VAR, int DEPTH>
@@ -2274,8 +2255,8 @@ void launch_confidence_d(int bd, const T* logits, int64_t n_rows, int64_t V, int
                                   : k_confidence<T, 256, VAR, DEPTH>;
   for (int64_t r = 0; r < n_rows; r += kConfMaxGrid) {
     const int64_t n = n_rows - r < kConfMaxGrid ? n_rows - r : kConfMaxGrid;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3((unsigned)bd), 0, st, logits + r * stride, n, V, stride, a,
-                       out + r, VAR ? var + r : nullptr);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3((unsigned)bd), 0, st, logits + r * stride, V, stride, a, out + r,
+                       VAR ? var + r : nullptr);
   }
 }
 template <typename T, bool VAR>
