@@ -225,7 +225,8 @@ cmsd_status cmsd_draft_len(const cmsd_row_stats* stats, int32_t batch, const cms
  *   n_accepted      device, batch int32 (output): accepted prefix length c_b in
  *                   [0, k_b]; -1 if the sequence's device inputs are invalid
  *                   (offsets inconsistent with draft_len or target_rows, draft_len
- *                   out of range, drafted id outside [0, vocab)).
+ *                   out of range, drafted id outside [0, vocab)).  May be draft_len's
+ *                   own buffer.
  *   next_token      device, batch int32 (output): the final token; -1 when invalid.
  *   workspace       device scratch of at least cmsd_verify_workspace_bytes(batch,
  *                   k_max, vocab) bytes, 8-byte aligned, owned by the caller: the
@@ -324,9 +325,10 @@ cmsd_status cmsd_set_row_events(void* const* row_events);
  * 256-thread workgroup; the last row of a sequence to finish (an atomic count per
  * sequence, behind the row's stored and acknowledged results) makes the draft
  * length and the accept tests and samples the final token in the same launch.  One
- * workgroup carries each sequence's final token, so the single launch is for rows
- * whose final-token work is tiny (1024 logits) and for callers that need exactly one
- * launch.  Arguments, outputs and errors are cmsd_logit_pass's
+ * workgroup carries each sequence's final token, so the single launch is for callers
+ * that need exactly one: cmsd_logit_pass (two launches for small batches) was as fast
+ * or faster at every size measured (one MI355X, us: 1024 logits 11.7 against 12.2, 32000
+ * 16.9 against 22.1 for one sequence and 26.4 against 40.4 for 64).  Arguments, outputs and errors are cmsd_logit_pass's
  * (cmsd_set_row_events does not apply to it), except the workspace:
  *   workspace       device scratch of at least
  *                   cmsd_logit_pass_fused_workspace_bytes(batch, k_max, vocab) bytes,

@@ -491,7 +491,7 @@ def cmsd_logit_pass_fused(draft_logits: torch.Tensor, target_logits: torch.Tenso
                           target_stats: torch.Tensor | None = None, n_accepted: torch.Tensor | None = None,
                           next_token: torch.Tensor | None = None, workspace: torch.Tensor | None = None,
                           stream=None) -> dict:
-    """cmsd_logit_pass in one launch, for small batches (a few hundred rows).  Same
+    """cmsd_logit_pass in one launch, for small batches of callers that need exactly one.  Same
     arguments and outputs; ``workspace`` must come from ``fused_workspace`` (or be
     zero-filled once before its first use) and is reused across calls."""
     if _native is not None and workspace is not None:

@@ -2005,8 +2005,9 @@ __global__ __launch_bounds__(kFinalBD) void k_final(VerifyArgs a, int S, int SW,
 // sets the counter back to zero.  The arithmetic is the four-launch pass's, so the outputs
 // are bit-identical to it.  For small batches: one compute unit does a sequence's final
 // token.  Device fences around the count, each a write-back of the L2, cost 30-50 ns of
-// the chip per workgroup; us with them and handed off, MI355X: 1 sequence of 4 drafts at
-// V = 1024 14.6 and 14.1, 8 of 8 drafts at V = 32000 23.8 and 22.3, 64 of them 148 and 39.
+// the chip per workgroup; us with them and, at the time, handed off, MI355X: 1 sequence of
+// 4 drafts at V = 1024 14.6 and 14.1 (now 12.4), 8 of 8 drafts at V = 32000 23.8 and 22.3,
+// 64 of them 148 and 39.
 constexpr int kFusedBD = 256;
 #ifndef CMSD_FUSED_SUB
 #define CMSD_FUSED_SUB 2
